@@ -6,8 +6,8 @@
 //
 // Arithmetic contract (shared by all kernels; compiled with
 // -ffp-contract=off): binary32, every operation of the step rounded in the
-// order written below; divisions are reciprocal products corrected to the
-// rounded quotient (see div_mass, div_rn).  sin and cos are polynomials on
+// order written below; divisions are products with reciprocals corrected to
+// the rounded quotient (see div_mass, div_small_angle, div_rn).  sin and cos are polynomials on
 // |theta| <= 1/4 (the only angles a non-terminated state can hold) and the
 // library routines beyond.
 #pragma once
@@ -171,25 +171,47 @@ __device__ __forceinline__ void sincos_th(float th, float &sn, float &c) {
 }
 
 // ---------------------------------------------------------------- division
-// Division by the total mass M = 1.1f: the product with the rounded
-// reciprocal, corrected once with the exact residual (Markstein).  Checked
-// against correctly rounded division for every finite binary32 dividend:
-// identical whenever |x| >= 2^-104; below that (where the quotient itself is
-// under 2^-104) the two may differ in the last place.
+// Division by the total mass M = 1.1f with two operations: 1/M held as the
+// sum of two binary32 numbers, x (hi + lo) accumulated in one fused
+// multiply-add (Brisebarre, Muller and Raina, "Accelerating correctly
+// rounded floating-point division when the divisor is known in advance",
+// IEEE Trans. Computers 53(8), 2004).  Checked against correctly rounded
+// division for every binary32 significand: identical whenever |x| >= 2^-104;
+// below that (where the low product underflows) the two may differ in the
+// last place.  One operation fewer than the product corrected by its exact
+// residual, which gives the same values.
 constexpr float kInvTotalMass = 1.0f / kTotalMass;
+constexpr float kInvTotalMassLo = float(1.0 / double(kTotalMass) - double(kInvTotalMass));
 
 __device__ __forceinline__ float div_mass(float x) {
-  const float q = x * kInvTotalMass;
-  const float r = __builtin_fmaf(-q, kTotalMass, x);
-  return __builtin_fmaf(r, kInvTotalMass, q);
+  return __builtin_fmaf(x, kInvTotalMass, x * kInvTotalMassLo);
 }
 
 // General division a / b: hardware reciprocal refined by one Newton step to
 // the rounded reciprocal, then the quotient corrected once with the exact
-// residual (Markstein's correction).  Used for the angular acceleration,
-// whose divisor lies in [0.62, 0.67].
+// residual (Markstein's correction).  Used for the angular acceleration where
+// the angle may be any (its divisor lies in [0.62, 0.67]).
 __device__ __forceinline__ float div_rn(float a, float b) {
   const float y0 = __builtin_amdgcn_rcpf(b);
+  const float e = __builtin_fmaf(-b, y0, 1.0f);
+  const float y = __builtin_fmaf(e, y0, y0);
+  const float q = a * y;
+  const float r = __builtin_fmaf(-q, b, a);
+  return __builtin_fmaf(r, y, q);
+}
+
+// a / b for the divisors of the angular acceleration at angles up to 1/4,
+// 0.621212 <= b <= 0.623995: there a line is within 3e-6 of 1/b, and one
+// Newton step from it gives the correctly rounded reciprocal for every
+// binary32 b of the range (checked exhaustively), so the quotient corrected
+// once with the exact residual is the correctly rounded quotient (Markstein).
+// Against div_rn (the same values there, checked exhaustively) a full-rate
+// multiply-add takes the place of the hardware reciprocal, which issues at a
+// quarter of the rate.
+constexpr float kRecipSlope = -0x1.4a3564p+1f, kRecipOffset = 0x1.9b2d86p+1f;
+
+__device__ __forceinline__ float div_small_angle(float a, float b) {
+  const float y0 = __builtin_fmaf(b, kRecipSlope, kRecipOffset);
   const float e = __builtin_fmaf(-b, y0, 1.0f);
   const float y = __builtin_fmaf(e, y0, y0);
   const float q = a * y;
@@ -203,11 +225,16 @@ __device__ __forceinline__ float div_rn(float a, float b) {
 //   temp  = (F + (pml * thd^2) * sin) / M
 //   thacc = (g sin - cos temp) / (l (4/3 - (mp cos^2) / M))
 //   xacc  = temp - ((pml * thacc) * cos) / M
+// l = 1/2 scales exactly, so the divisor of thacc is formed from halved
+// constants instead of multiplied by l: the same value.
 __device__ __forceinline__ float force_of(uint32_t a) { return a ? kForceMag : -kForceMag; }
 
+static_assert(kHalfLength == 0.5f, "the divisor's exact scaling");
+
 // kLimited: the angle is one a step produces -- within the 12-degree limit,
-// or NaN -- so the polynomials alone give the same values (a NaN angle gives
-// NaN either way); a caller's state may hold any angle (kLimited false).
+// or NaN -- so the polynomials and the small-angle division alone give the
+// same values (a NaN angle gives NaN either way); a caller's state may hold
+// any angle (kLimited false).
 template <bool kLimited = false>
 __device__ __forceinline__ State dynamics(State s, float force) {
   float sn, c;
@@ -220,8 +247,9 @@ __device__ __forceinline__ State dynamics(State s, float force) {
   const float thd2 = s.thd * s.thd;
   const float c2 = c * c;
   const float temp = div_mass(force + kPoleMassLength * thd2 * sn);
-  const float thacc =
-      div_rn(kGravity * sn - c * temp, kHalfLength * (kFourThirds - div_mass(kMassPole * c2)));
+  const float num = kGravity * sn - c * temp;
+  const float den = kHalfLength * kFourThirds - div_mass((kHalfLength * kMassPole) * c2);
+  const float thacc = kLimited ? div_small_angle(num, den) : div_rn(num, den);
   const float xacc = temp - div_mass(kPoleMassLength * thacc * c);
   State o;
   o.x = s.x + kTau * s.xd;

@@ -104,6 +104,9 @@ __device__ __forceinline__ void stage_w2_fragments(const uint16_t *w, bf16x4 *w2
 }
 
 struct MlpPolicy {
+  // one copy of a step's code in the loop: eight would not fit the
+  // instruction cache
+  static constexpr bool kUnrolled = false;
   bf16x4 w1[4];       // W1^T rows 16m..16m+15, K = the 4 inputs (lane group 0 only)
   bf16x4 w3[4];       // W3^T rows 0,1 (lanes c < 2), K chunk 16c..
   const bf16x4 *w2f;  // W2^T fragments in LDS (stage_w2_fragments)
@@ -120,9 +123,11 @@ struct MlpPolicy {
     }
   }
 
+  __device__ __forceinline__ void prepare(uint32_t, bool) {}
+
   // Action of the lane's environment for its pre-step state s.  Called by
   // every lane of the wave.
-  __device__ __forceinline__ uint32_t operator()(uint32_t, uint32_t, const State &s) {
+  __device__ __forceinline__ uint32_t operator()(uint32_t, const State &s) {
     const uint32_t lane = threadIdx.x & 63u, g = lane >> 4, c = lane & 15u;
     const uint32_t o01 = pack2(s.x, s.xd), o23 = pack2(s.th, s.thd);
     const f32x4 zero = {0.f, 0.f, 0.f, 0.f};
@@ -175,7 +180,7 @@ struct MlpPolicy {
   }
 };
 
-template <bool kTraj>
+template <Traj kTraj>
 __global__ __launch_bounds__(kResidentBlock) void k_resident_policy(RolloutParams p) {
   __shared__ uint16_t w[kWeights];
   __shared__ bf16x4 w2f[kW2Frags];
@@ -213,7 +218,7 @@ __global__ __launch_bounds__(kResidentBlock) void k_policy_actions(
     // plane offsets in 64 bits: 3n passes 2^32 from n > 1,431,655,765
     const size_t m = n;
     const State s{obs[ic], obs[m + ic], obs[2u * m + ic], obs[3u * m + ic]};
-    const uint32_t a = policy(0u, 0u, s);
+    const uint32_t a = policy(0u, s);
     if (i < n) actions[i] = uint8_t(a);
   }
 }
@@ -230,12 +235,18 @@ hipError_t launch_policy_actions(const float *obs, uint32_t n, const uint16_t *p
 }
 
 hipError_t launch_resident_policy(const RolloutParams &p, hipStream_t stream) {
-  const bool traj = p.obs || p.reward || p.done;
-  const dim3 grid((p.n + kResidentBlock - 1) / kResidentBlock);
-  if (traj)
-    hipLaunchKernelGGL(k_resident_policy<true>, grid, dim3(kResidentBlock), 0, stream, p);
-  else
-    hipLaunchKernelGGL(k_resident_policy<false>, grid, dim3(kResidentBlock), 0, stream, p);
+  const dim3 grid((p.n + kResidentBlock - 1) / kResidentBlock), b(kResidentBlock);
+  switch (traj_kind(p, sizeof(float))) {
+    case Traj::kNone:
+      hipLaunchKernelGGL(k_resident_policy<Traj::kNone>, grid, b, 0, stream, p);
+      break;
+    case Traj::kAny:
+      hipLaunchKernelGGL(k_resident_policy<Traj::kAny>, grid, b, 0, stream, p);
+      break;
+    case Traj::kAll:
+      hipLaunchKernelGGL(k_resident_policy<Traj::kAll>, grid, b, 0, stream, p);
+      break;
+  }
   return hipGetLastError();
 }
 

@@ -7,11 +7,12 @@
 // Arithmetic contract (compiled with -ffp-contract=off):
 //   binary64 -- every operation rounded once in binary64, in the operation
 //     order of the binary32 step; the three divisions by the total mass M are
-//     the product with RN(1/M) corrected once with the exact residual
-//     (Markstein: the correctly rounded quotient away from underflow), the
-//     angular-acceleration division is the IEEE division; sin and cos are
-//     Taylor polynomials on |theta| <= 1/4 (within an ulp) and the device
-//     library's binary64 routines beyond.
+//     products with 1/M held as a sum of two numbers (the correctly rounded
+//     quotient away from underflow), the angular-acceleration division is a
+//     product with a Newton reciprocal corrected by its exact residual at
+//     angles up to 1/4 and the IEEE division beyond; sin and cos are Taylor
+//     polynomials on |theta| <= 1/4 (within an ulp) and the device library's
+//     binary64 routines beyond.
 //   binary16 -- constants rounded once from their exact values; additions,
 //     subtractions and products are binary16 instructions (one rounding
 //     each); a quotient is the binary32 quotient rounded once to binary16,
@@ -97,22 +98,37 @@ __device__ __forceinline__ void sincos64(double th, double &sn, double &c) {
   }
 }
 
-// Division by the total mass M = 1.1 (binary64): the product with the
-// rounded reciprocal, corrected once with the exact residual.  By
-// Markstein's theorem (a reciprocal within half an ulp and a quotient
-// within one ulp give, after one fused correction, the rounded quotient)
-// this is the correctly rounded x / M whenever nothing underflows, i.e. for
-// |x| above about 2^-960; the binary64 step's dividends are of order 1e-3..10.
+// Division by the total mass M = 1.1 (binary64): x (hi + lo) with 1/M =
+// hi + lo to about 2^-107, accumulated in one fused multiply-add, as in
+// binary32.  The only dividends whose quotients lie close enough to a
+// rounding boundary for that to matter are a few significands, found by
+// solving for them and all rounded correctly, so this is the correctly rounded
+// x / M whenever nothing underflows, i.e. for |x| above about 2^-960; the
+// binary64 step's dividends are of order 1e-3..10.
 constexpr double kTotalMass64 = 0.1 + 1.0;
 constexpr double kInvTotalMass64 = 1.0 / kTotalMass64;
+constexpr double kInvTotalMassLo64 = -0x1.8dc08767ab5f2p-55;  // RN(1/M - RN(1/M))
 
 __device__ __forceinline__ double div_mass64(double x) {
-  const double q = x * kInvTotalMass64;
-  const double r = __builtin_fma(-q, kTotalMass64, x);
-  return __builtin_fma(r, kInvTotalMass64, q);
+  return __builtin_fma(x, kInvTotalMass64, x * kInvTotalMassLo64);
 }
 
-// kLimited as for dynamics: an angle within the limit or NaN.
+// a / b for the divisors of the angular acceleration at angles up to 1/4,
+// 0.6212 < b < 0.6240: a line within 3e-6 of 1/b and two Newton steps give
+// the reciprocal to half an ulp and 1e-22, the quotient is corrected once
+// with the exact residual: the correctly rounded quotient unless a / b lies
+// within about 2^-105 of a rounding boundary.  Eight multiply-adds instead
+// of the IEEE sequence's scaling, quarter-rate reciprocal and fix-up.
+__device__ __forceinline__ double div_small_angle64(double a, double b) {
+  const double y0 = __builtin_fma(b, double(kRecipSlope), double(kRecipOffset));
+  const double y1 = __builtin_fma(__builtin_fma(-b, y0, 1.0), y0, y0);
+  const double y = __builtin_fma(__builtin_fma(-b, y1, 1.0), y1, y1);
+  const double q = a * y;
+  const double r = __builtin_fma(-q, b, a);
+  return __builtin_fma(r, y, q);
+}
+
+// kLimited as for dynamics.
 template <bool kLimited = false>
 __device__ __forceinline__ State64 dynamics64(const State64 &s, double force) {
   const double g = 9.8, mp = 0.1, l = 0.5, tau = 0.02;
@@ -127,7 +143,9 @@ __device__ __forceinline__ State64 dynamics64(const State64 &s, double force) {
   const double thd2 = s.thd * s.thd;
   const double c2 = c * c;
   const double temp = div_mass64(force + pml * thd2 * sn);
-  const double thacc = (g * sn - c * temp) / (l * (four3 - div_mass64(mp * c2)));
+  const double num = g * sn - c * temp;
+  const double den = l * four3 - div_mass64((l * mp) * c2);
+  const double thacc = kLimited ? div_small_angle64(num, den) : num / den;
   const double xacc = temp - div_mass64(pml * thacc * c);
   return State64{s.x + tau * s.xd, s.xd + tau * xacc, s.th + tau * s.thd, s.thd + tau * thacc};
 }
@@ -210,10 +228,16 @@ __device__ __forceinline__ bool near_f16_midpoint(float s) {
 // sin and cos of a binary16 angle rounded once to binary16: the binary32
 // values rounded, unless either lies next to a binary16 midpoint (about one
 // evaluation in 2^11); then the rounding is settled from the binary64
-// values.
+// values.  kLimited as for dynamics.
+template <bool kLimited = false>
 __device__ __forceinline__ void sincos16(half_t th, half_t &sn, half_t &c) {
   float sf, cf;
-  sincos_th(float(th), sf, cf);
+  if (kLimited) {
+    sf = sin_small(float(th));
+    cf = cos_small(float(th));
+  } else {
+    sincos_th(float(th), sf, cf);
+  }
   sn = to_half(sf);
   c = to_half(cf);
   if (near_f16_midpoint(sf) || near_f16_midpoint(cf)) {
@@ -224,12 +248,13 @@ __device__ __forceinline__ void sincos16(half_t th, half_t &sn, half_t &c) {
   }
 }
 
+template <bool kLimited = false>
 __device__ __forceinline__ State16 dynamics16(const State16 &s, half_t force) {
   const half_t g = half_t(9.8), mp = half_t(0.1), l = half_t(0.5);
   const half_t tau = half_t(0.02), four3 = half_t(4.0 / 3.0);
   const half_t pml = mp * l;  // the total mass RN16(mp + mc) is kTotalMass16
   half_t sn, c;
-  sincos16(s.th, sn, c);
+  sincos16<kLimited>(s.th, sn, c);
   const half_t thd2 = s.thd * s.thd;
   const half_t c2 = c * c;
   const half_t temp = div16_mass(force + pml * thd2 * sn);
@@ -246,9 +271,9 @@ struct PrecF16 {
     const State f = reset_draw(key, env, k);
     return S{to_half(f.x), to_half(f.xd), to_half(f.th), to_half(f.thd)};
   }
-  template <bool kLimited = false>  // the binary16 step makes no use of it
+  template <bool kLimited = false>
   __device__ static __forceinline__ S step(const S &s, uint32_t a) {
-    return dynamics16(s, a ? half_t(10.0) : half_t(-10.0));
+    return dynamics16<kLimited>(s, a ? half_t(10.0) : half_t(-10.0));
   }
   __device__ static __forceinline__ bool done(const S &s) {
     const half_t xl = half_t(2.4), tl = half_t(kThetaLimit64);

@@ -5,12 +5,11 @@
 // VGPRs.  Per step: the action (from the policy functor), dynamics,
 // termination; on termination the lane swaps in the start state of its next
 // episode, drawn ahead of time, and the lanes that used theirs draw the next
-// one in a batched pass every kRefill steps.  The wave counts its
-// terminations with a ballot into a scalar register; at the end the block
-// combines its waves in LDS and publishes the totals with one atomic pair.
+// one in a batched pass every kRefill steps.
 #pragma once
 
 #include <type_traits>
+#include <utility>
 
 #include "cp_launch.h"
 #include "cp_precision.h"
@@ -20,12 +19,32 @@ namespace cp {
 constexpr int kResidentBlock = 256;
 constexpr int kResidentWaves = kResidentBlock / 64;
 
-// Refill period of the prefetched reset states.  An episode drawn from the
-// reset distribution lasts at least 8 steps, so a lane that used its
-// prefetched start state gets the next one before it can terminate again;
-// the per-lane fallback in the loop keeps results exact for any episode
-// length.
+// Refill period of the prefetched reset states: no episode started from the
+// reset distribution ends before its kRefill-th step, so between two refills
+// at most kRefill steps apart a lane ends at most one episode and its
+// prefetched start state is always there.
 constexpr uint32_t kRefill = 8u;
+
+// Largest |theta| that `steps` steps from the reset distribution (every
+// variable within 0.05) can reach: every term of the angular acceleration
+// taken with the sign and size that grow it (sin x <= x, |cos| <= 1, the
+// divisor at its smallest, at cos = 1) and one percent added to each step
+// for rounding in any of the precisions.
+constexpr double largest_angle(uint32_t steps) {
+  const double g = 9.8, mp = 0.1, m = 1.1, l = 0.5, tau = 0.02;
+  double th = 0.05, thd = 0.05;
+  for (uint32_t k = 0; k < steps; ++k) {
+    const double temp = (10.0 + mp * l * thd * thd * th) / m;
+    const double acc = (g * th + temp) / (l * (4.0 / 3.0 - mp / m));
+    const double th1 = th + tau * thd;
+    thd = 1.01 * (thd + tau * acc);
+    th = 1.01 * th1;
+  }
+  return th;
+}
+// (x, from 0.05 at 0.05 per second and below 12 per second^2, stays far
+// inside 2.4 meanwhile)
+static_assert(largest_angle(kRefill - 1u) < 0.2094, "an episode may end within a refill period");
 
 __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
 #pragma unroll
@@ -77,24 +96,27 @@ __device__ __forceinline__ void block_publish(unsigned long long *global, unsign
 // two blocks and computes both.
 template <bool kAligned>
 struct HashPolicy {
+  static constexpr bool kUnrolled = true;  // the rounds of kRefill steps
   U2 key;
   uint32_t env, g0;
-  U2 b0, b1;  // this lane's blocks for step base + lane
-  uint32_t base;
+  U2 b0, b1;  // this lane's blocks for step (t & ~63) + lane
 
   __device__ __forceinline__ HashPolicy(U2 k, uint32_t e) : key(k), env(e) {
     g0 = uint32_t(__builtin_amdgcn_readfirstlane(int(e))) >> 6;  // logical shift: e may be >= 2^31
   }
 
+  // Called before the first step of a launch and before the steps whose
+  // index is a multiple of kRefill.
+  __device__ __forceinline__ void prepare(uint32_t t, bool first) {
+    if (!first && (t & 63u) != 0u) return;
+    const uint32_t step = (t & ~63u) + (threadIdx.x & 63u);
+    b0 = threefry2x32(key.a, key.b, g0, step);
+    if (!kAligned) b1 = threefry2x32(key.a, key.b, g0 + 1u, step);
+  }
+
   template <class St>
-  __device__ __forceinline__ uint32_t operator()(uint32_t j, uint32_t t, const St &) {
-    if (j == 0u || (t & 63u) == 0u) {
-      base = t & ~63u;
-      const uint32_t step = base + (threadIdx.x & 63u);
-      b0 = threefry2x32(key.a, key.b, g0, step);
-      if (!kAligned) b1 = threefry2x32(key.a, key.b, g0 + 1u, step);
-    }
-    const int src = int(t - base);
+  __device__ __forceinline__ uint32_t operator()(uint32_t t, const St &) {
+    const int src = int(t & 63u);
     U2 w{uint32_t(__builtin_amdgcn_readlane(int(b0.a), src)),
          uint32_t(__builtin_amdgcn_readlane(int(b0.b), src))};
     if (kAligned) {
@@ -112,36 +134,104 @@ struct HashPolicy {
   }
 };
 
-// Stores of the j-th step of a trajectory: obs [T][4][n] in the state's
-// type, reward [T][n] f32, done [T][n] u8.  Each plane's base for the step
-// is wave-uniform (scalar arithmetic); kOff32 (every byte offset within a
-// plane below 2^32) takes the scalar-base form with the lane's fixed 32-bit
-// offset, otherwise 64-bit vector addresses.  Plain (write-back) stores:
-// the waves of a launch are at different steps at any moment, so each
-// writes its pieces of many planes far apart, and non-temporal stores of
-// those pieces measured 10-15% slower (7.2 against 6.2-6.5 ms for
-// 16,777,216 x 100) than stores the L2 merges into whole lines first.
-template <bool kOff32, class T, class S>
-__device__ __forceinline__ void store_traj(const RolloutParams &p, T *pobs, uint32_t j, uint32_t i,
-                                           const S &s, bool d) {
-  const size_t plane = size_t(j) * p.n;
-  if (p.obs) {
-    T *const ob = pobs + 4u * plane;
-    *elem<kOff32>(ob, i) = s.x;
-    *elem<kOff32>(ob + p.n, i) = s.xd;
-    *elem<kOff32>(ob + 2u * size_t(p.n), i) = s.th;
-    *elem<kOff32>(ob + 3u * size_t(p.n), i) = s.thd;
-  }
-  if (p.reward) *elem<kOff32>(p.reward + plane, i) = 1.0f;
-  if (p.done) *elem<kOff32>(p.done + plane, i) = uint8_t(d);
+// What a launch stores per step: nothing, whichever of obs [T][4][n] (in the
+// state's type), reward [T][n] f32 and done [T][n] u8 are given, or all three
+// with every byte offset within a plane below 2^32 (no tests in the loop).
+enum class Traj { kNone, kAny, kAll };
+
+inline Traj traj_kind(const RolloutParams &p, size_t elem) {
+  if (!p.obs && !p.reward && !p.done) return Traj::kNone;
+  const bool off32 = uint64_t(p.n) * (elem > 4 ? elem : 4) <= (uint64_t(1) << 32);
+  return p.obs && p.reward && p.done && off32 ? Traj::kAll : Traj::kAny;
 }
 
-// The loop.  `policy(j, t, s)` returns the action of step t (j-th of this
-// rollout) for the lane's pre-step state s; it is called by every lane of
-// the wave at every step (policies may use cross-lane operations).  P is
-// the precision of the state, the step and the obs trajectory (the state
-// and obs pointers of p point at P::T values).
-template <bool kTraj, class Policy, class P = PrecF32>
+// Stores of one step (obs, reward and done: the step's rows).  Each plane's
+// base is wave-uniform (scalar arithmetic); kOff32 takes the scalar-base form
+// with the lane's fixed 32-bit offset, otherwise 64-bit vector addresses.
+// Plain (write-back) stores: the waves of a launch are at different steps at
+// any moment, so each writes its pieces of many planes far apart, and
+// non-temporal stores of those pieces measured 10-15% slower (7.2 against
+// 6.2-6.5 ms for 16,777,216 x 100) than stores the L2 merges into whole lines
+// first.
+template <bool kAll, bool kOff32, class T, class S>
+__device__ __forceinline__ void store_traj(T *obs, float *reward, uint8_t *done, uint32_t n,
+                                           uint32_t i, const S &s, bool d) {
+  if (kAll || obs) {
+    *elem<kOff32>(obs, i) = s.x;
+    *elem<kOff32>(obs + n, i) = s.xd;
+    *elem<kOff32>(obs + 2u * size_t(n), i) = s.th;
+    *elem<kOff32>(obs + 3u * size_t(n), i) = s.thd;
+  }
+  if (kAll || reward) *elem<kOff32>(reward, i) = 1.0f;
+  if (kAll || done) *elem<kOff32>(done, i) = uint8_t(d);
+}
+
+// On the lanes of `m` (wave-uniform): s = nxt, and lr = r.  Written as moves
+// under the mask: a move issues at twice the rate of a select, and selects
+// one after the other on the same condition at a fraction of it (measured:
+// 4.3 moves, 2.3 selects on a scalar mask, 0.4 successive selects on vcc per
+// CU and ns).  r: an integral_constant or a wave-uniform number.
+#define CP_TAKE(mov, r_constraint, r_value)                                                       \
+  unsigned long long saved;                                                                       \
+  asm volatile(                                                                                   \
+      "s_and_saveexec_b64 %[sv], %[m]\n\t" mov " %[x], %[nx]\n\t" mov " %[xd], %[nxd]\n\t" mov     \
+      " %[th], %[nth]\n\t" mov " %[thd], %[nthd]\n\tv_mov_b32 %[lr], %[r]\n\ts_mov_b64 exec, %[sv]" \
+      : [x] "+v"(s.x), [xd] "+v"(s.xd), [th] "+v"(s.th), [thd] "+v"(s.thd), [lr] "+v"(lr),        \
+        [sv] "=&s"(saved)                                                                         \
+      : [m] "s"(m), [nx] "v"(nxt.x), [nxd] "v"(nxt.xd), [nth] "v"(nxt.th), [nthd] "v"(nxt.thd),   \
+        [r] r_constraint(r_value)                                                                 \
+      : "scc")
+
+template <int r>
+__device__ __forceinline__ void take(unsigned long long m, State &s, const State &nxt,
+                                     uint32_t &lr, std::integral_constant<int, r>) {
+  CP_TAKE("v_mov_b32", "i", r);
+}
+__device__ __forceinline__ void take(unsigned long long m, State &s, const State &nxt,
+                                     uint32_t &lr, uint32_t r) {
+  CP_TAKE("v_mov_b32", "s", r);
+}
+template <int r>
+__device__ __forceinline__ void take(unsigned long long m, State64 &s, const State64 &nxt,
+                                     uint32_t &lr, std::integral_constant<int, r>) {
+  CP_TAKE("v_mov_b64", "i", r);
+}
+__device__ __forceinline__ void take(unsigned long long m, State64 &s, const State64 &nxt,
+                                     uint32_t &lr, uint32_t r) {
+  CP_TAKE("v_mov_b64", "s", r);
+}
+#undef CP_TAKE
+__device__ __forceinline__ void take(unsigned long long m, State16 &s, const State16 &nxt,
+                                     uint32_t &lr, uint32_t r) {
+  if (__builtin_amdgcn_inverse_ballot_w64(m)) {
+    s = nxt;
+    lr = r;
+  }
+}
+
+// f(integral_constant 0), ..., f(integral_constant kCount - 1)
+template <class F, int... r>
+__device__ __forceinline__ void each_of(F &f, std::integer_sequence<int, r...>) {
+  (f(std::integral_constant<int, r>{}), ...);
+}
+
+// The loop.  `policy(t, s)` returns the action of step t for the lane's
+// pre-step state s; it is called by every lane of the wave at every step
+// (policies may use cross-lane operations).  P is the precision of the
+// state, the step and the obs trajectory (the state and obs pointers of p
+// point at P::T values).
+//
+// What bounds it is vector issue (the trajectory form: its stores), so the
+// step is kept to the arithmetic, two compares, the action's lane reads and
+// select and five moves: the episode length is not counted (the step of the
+// latest termination is kept instead), the episode index is brought up to
+// date at the refills only, and rounds start at multiples of kRefill of the
+// global step, so that the generator test runs once per round.  Measured with
+// the divisions' cheaper forms against the earlier loop (length counted,
+// selects, a second termination tested for at every step): 1,048,576 x 1,000
+// in binary32 1.293 -> 1.227 ms, in binary64 2.54 -> 2.04 ms; 1,024 x 200,
+// where a step costs one wave's instruction stream, 41.8 -> 33.4 us.
+template <Traj kTraj, class Policy, class P = PrecF32>
 __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy &policy) {
   using T = typename P::T;
   using S = typename P::S;
@@ -149,60 +239,68 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   T *const pxd = reinterpret_cast<T *>(p.xd);
   T *const pth = reinterpret_cast<T *>(p.th);
   T *const pthd = reinterpret_cast<T *>(p.thd);
-  T *const pobs = reinterpret_cast<T *>(p.obs);
   const uint32_t i = blockIdx.x * kResidentBlock + threadIdx.x;
-  // every byte offset within a trajectory plane (at most max(sizeof(T), 4)
-  // bytes per environment) below 2^32
   const bool off32 = uint64_t(p.n) * (sizeof(T) > 4 ? sizeof(T) : 4) <= (uint64_t(1) << 32);
   const bool valid = i < p.n;
   const uint32_t env = p.env_base + i;
-  // Lanes past the end run the loop on a dummy state (the wave stays
-  // converged for the ballots), never terminate and store nothing.
-  S s{T(0), T(0), T(0), T(0)};
+  // Lanes past the end run the loop on a NaN state (the wave stays converged
+  // for the cross-lane operations): it never terminates.  They store nothing.
+  const T nan = T(__builtin_nanf(""));
+  S s{nan, nan, nan, nan};
   uint32_t k0 = 0u, len0 = 0u;
   if (valid) {
     s = S{px[i], pxd[i], pth[i], pthd[i]};
     k0 = p.ep_index[i];
     len0 = p.ep_len[i];
   }
-  // The episode index is brought up to date at the refills only: while
-  // `have` holds the lane is in episode k, after a termination that used the
-  // prefetched start state it is in episode k + 1.
-  uint32_t k = k0, len = len0;
-  // Start state of the next episode, drawn ahead of time so that a
-  // termination costs a select; `have` says whether it is drawn yet.
+  // The lane is in episode k, or in k + 1 if its bit of `used` is set: it
+  // ended an episode since the last refill, at the lr-th step after it, and
+  // used the prefetched start state nxt (of episode k + 1).
+  uint32_t k = k0, lr = 0u, last = 0u;
+  unsigned long long used = 0u;
   S nxt = P::draw(p.krst, env, k + 1u);
-  bool have = true;
-  // One step (the j-th of this rollout); `limited`: the state is one a step
-  // produced (every step after a launch's first), its angle within the
-  // limit or NaN.
-  auto step = [&](uint32_t j, auto limited) {
-    const uint32_t t = p.t0 + j;
-    const uint32_t a = policy(j, t, s);
+  // rows of the step's trajectory outputs
+  T *row_obs = reinterpret_cast<T *>(p.obs);
+  float *row_reward = p.reward;
+  uint8_t *row_done = p.done;
+  // One step at global index t, the r-th after the last refill; `limited`:
+  // the state is one a step produced (every step after a launch's first), its
+  // angle within the limit or NaN.
+  auto step = [&](uint32_t t, auto r, auto limited) {
+    const uint32_t a = policy(t, s);
     S o = P::template step<decltype(limited)::value>(s, a);
-    const bool d = valid && P::done(o);
-    len = d ? 0u : len + 1u;
-    if (d && !have) {  // second termination before a refill
-      k += 1u;
-      nxt = P::draw(p.krst, env, k + 1u);
-    }
-    if (d) o = nxt;
-    have = have && !d;
+    const bool d = P::done(o);
+    const unsigned long long m = __builtin_amdgcn_ballot_w64(d);
+    take(m, o, nxt, lr, r);
+    used |= m;
     s = o;
-    if (kTraj && valid) {
-      if (off32) store_traj<true>(p, pobs, j, i, s, d);
-      else store_traj<false>(p, pobs, j, i, s, d);
+    if constexpr (kTraj != Traj::kNone) {
+      if (valid) {
+        if (kTraj == Traj::kAll || off32)
+          store_traj<kTraj == Traj::kAll, true>(row_obs, row_reward, row_done, p.n, i, s, d);
+        else
+          store_traj<false, false>(row_obs, row_reward, row_done, p.n, i, s, d);
+      }
+      if (kTraj == Traj::kAll || row_obs) row_obs += 4u * size_t(p.n);
+      if (kTraj == Traj::kAll || row_reward) row_reward += p.n;
+      if (kTraj == Traj::kAll || row_done) row_done += p.n;
     }
   };
-  // The refill after a round: the lanes that used their prefetched state
-  // (about a third of them after kRefill steps) get the start state of the
-  // episode after their current one, each wave drawing for its own lanes.
-  auto refill_wave = [&]() {
-    if (!have) {
+  // After the steps from the j-th of this launch on: the lanes that ended an
+  // episode (about a third of them after kRefill steps) count it.
+  auto count = [&](uint32_t j) {
+    const bool mine = __builtin_amdgcn_inverse_ballot_w64(used);
+    used = 0u;
+    if (mine) {
       k += 1u;
-      nxt = P::draw(p.krst, env, k + 1u);
-      have = true;
+      last = j + lr;
     }
+    return mine;
+  };
+  // ... and draw the start state of the episode after their current one,
+  // each wave for its own lanes.
+  auto refill_wave = [&](uint32_t j) {
+    if (used != 0u && count(j)) nxt = P::draw(p.krst, env, k + 1u);
   };
   // The same refill served by the block together, for the kernel writing a
   // trajectory (bound by its stores, where fewer vector instructions mean
@@ -216,12 +314,12 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   // the wave counts are double-buffered by round, so that a round's counts
   // are never overwritten while a wave may still read them.
   uint32_t parity = 0u;
-  auto refill_block = [&]() {
+  auto refill_block = [&](uint32_t j) {
     __shared__ uint32_t wave_cnt[2][kResidentWaves];
     __shared__ uint32_t req_env[kResidentBlock], req_k[kResidentBlock];
     __shared__ S got[kResidentBlock];
     const uint32_t wave = threadIdx.x >> 6;
-    const unsigned long long m = __ballot(!have);
+    const unsigned long long m = used;
     if ((threadIdx.x & 63u) == 0u) wave_cnt[parity][wave] = uint32_t(__popcll(m));
     __syncthreads();
     uint32_t base = 0u, total = 0u;
@@ -235,38 +333,59 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     if (total == 0u) return;  // the same for the whole block
     const uint32_t slot =
         base + __builtin_amdgcn_mbcnt_hi(uint32_t(m >> 32), __builtin_amdgcn_mbcnt_lo(uint32_t(m), 0u));
-    if (!have) {
-      k += 1u;
+    const bool mine = count(j);
+    if (mine) {
       req_env[slot] = env;
       req_k[slot] = k + 1u;
     }
     __syncthreads();
     if (threadIdx.x < total) got[threadIdx.x] = P::draw(p.krst, req_env[threadIdx.x], req_k[threadIdx.x]);
     __syncthreads();
-    if (!have) {
-      nxt = got[slot];
-      have = true;
-    }
+    if (mine) nxt = got[slot];
   };
-  // The launch's first step (any state), then rounds of kRefill steps
-  // (unrolled: the refill test and the loop control once per round), each
-  // followed by the refill, then the remaining steps.
+  auto refill = [&](uint32_t j) {
+    if constexpr (kTraj != Traj::kNone) refill_block(j);
+    else refill_wave(j);
+  };
+  // The launch's first step (any state), single steps up to a multiple of
+  // kRefill, rounds of kRefill steps (unrolled), the remaining steps; a
+  // refill after each of these groups.
   using any_angle = std::integral_constant<bool, false>;
   using limited_angle = std::integral_constant<bool, true>;
-  if (p.T > 0u) step(0u, any_angle{});
-  uint32_t j = 1;
+  uint32_t j = 0u;  // steps done; `first`: first step of the group
+  auto singles = [&](uint32_t end) {
+    const uint32_t first = j;
+    for (; j < end; ++j) step(p.t0 + j, j - first, limited_angle{});
+    refill(first);
+  };
+  policy.prepare(p.t0, true);
+  step(p.t0, 0u, any_angle{});
+  j = 1u;
+  refill(0u);
+  const uint32_t lead = (0u - (p.t0 + 1u)) & (kRefill - 1u);
+  if (lead != 0u) singles(p.T < 1u + lead ? p.T : 1u + lead);
   for (; j + kRefill <= p.T; j += kRefill) {
-#pragma unroll
-    for (uint32_t r = 0; r < kRefill; ++r) step(j + r, limited_angle{});
-    if constexpr (kTraj) refill_block();
-    else refill_wave();
+    const uint32_t t = p.t0 + j;
+    policy.prepare(t, false);
+    if constexpr (Policy::kUnrolled) {
+      auto one = [&](auto r) { step(t + uint32_t(decltype(r)::value), r, limited_angle{}); };
+      each_of(one, std::make_integer_sequence<int, int(kRefill)>{});
+    } else {
+#pragma unroll 1
+      for (uint32_t r = 0; r < kRefill; ++r) step(t + r, r, limited_angle{});
+    }
+    refill(j);
   }
-  for (; j < p.T; ++j) step(j, limited_angle{});
-  if (!have) k += 1u;
+  if (j < p.T) {
+    policy.prepare(p.t0 + j, false);
+    singles(p.T);
+  }
   // Over the rollout an environment's terminations are the growth of its
-  // episode index and its finished returns are T + len(start) - len(end);
-  // the summed reward of T steps (1 each, accumulated in binary32) is T up
-  // to 2^24, where the binary32 sum stops growing.
+  // episode index, its episode length counts from its latest termination and
+  // its finished returns are T + len(start) - len(end); the summed reward of T
+  // steps (1 each, accumulated in binary32) is T up to 2^24, where the
+  // binary32 sum stops growing.
+  const uint32_t len = k != k0 ? p.T - 1u - last : len0 + p.T;
   const uint32_t n_done = k - k0;
   const uint32_t returns = p.T + len0 - len;
   if (valid) {

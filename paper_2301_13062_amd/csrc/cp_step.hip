@@ -562,7 +562,7 @@ hipError_t rollout_graph(const RolloutKey &k, RolloutGraph **out) {
   return hipSuccess;
 }
 
-template <bool kTraj, class P, bool kAligned>
+template <Traj kTraj, class P, bool kAligned>
 __global__ __launch_bounds__(kResidentBlock) void k_resident(RolloutParams p) {
   HashPolicy<kAligned> policy(p.kact, p.env_base + blockIdx.x * kResidentBlock + threadIdx.x);
   resident_rollout<kTraj, HashPolicy<kAligned>, P>(p, policy);
@@ -712,12 +712,18 @@ hipError_t launch_concat_step(const StepParams &p, void *workspace, hipStream_t 
 
 template <class P, bool kAligned>
 static void resident_as(const RolloutParams &p, hipStream_t stream) {
-  const bool traj = p.obs || p.reward || p.done;
-  const dim3 grid((p.n + kResidentBlock - 1) / kResidentBlock);
-  if (traj)
-    hipLaunchKernelGGL((k_resident<true, P, kAligned>), grid, dim3(kResidentBlock), 0, stream, p);
-  else
-    hipLaunchKernelGGL((k_resident<false, P, kAligned>), grid, dim3(kResidentBlock), 0, stream, p);
+  const dim3 grid((p.n + kResidentBlock - 1) / kResidentBlock), b(kResidentBlock);
+  switch (traj_kind(p, sizeof(typename P::T))) {
+    case Traj::kNone:
+      hipLaunchKernelGGL((k_resident<Traj::kNone, P, kAligned>), grid, b, 0, stream, p);
+      break;
+    case Traj::kAny:
+      hipLaunchKernelGGL((k_resident<Traj::kAny, P, kAligned>), grid, b, 0, stream, p);
+      break;
+    case Traj::kAll:
+      hipLaunchKernelGGL((k_resident<Traj::kAll, P, kAligned>), grid, b, 0, stream, p);
+      break;
+  }
 }
 
 template <class P>
