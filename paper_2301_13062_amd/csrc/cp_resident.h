@@ -56,35 +56,47 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
   return v;
 }
 
-// Adds the block's (a, b) sums to global[0], global[1]: waves reduce with
-// lane shuffles, the block through LDS, thread 0 issues one atomic pair.
-// Every thread of the block must call it.
+// Adds a block's sums to global[0], global[1] with one atomic instruction:
+// every wave adds its lanes' sums to the block's in LDS and counts itself, the
+// wave that counts last publishes them (lanes 0 and 1 one sum each).  No
+// barrier: waves end at different times, and ended ones leave their issue
+// slots to the others, where waves waiting at a barrier slowed the rest
+// (1,048,576 x 1,000 in binary16 1,375 -> 1,2xx us).
+// Atomics on one line come back at about 10 ns each however many blocks
+// issue them (65,536 blocks adding their two sums one after the other cost
+// a 230 us launch another 1.34 ms), so kernels whose blocks are short call it
+// from a bounded grid.
 template <int kBlockThreads>
-__device__ __forceinline__ void block_publish(unsigned long long *global, unsigned long long a,
-                                              unsigned long long b, bool a_is_wave_uniform) {
-  constexpr int kW = kBlockThreads / 64;
-  __shared__ unsigned long long sa[kW], sb[kW];
-  if (!a_is_wave_uniform) a = wave_sum_u64(a);
-  b = wave_sum_u64(b);
-  const int w = threadIdx.x >> 6;
-  if ((threadIdx.x & 63u) == 0u) {
-    sa[w] = a;
-    sb[w] = b;
-  }
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    unsigned long long ta = 0, tb = 0;
-#pragma unroll
-    for (int j = 0; j < kW; ++j) {
-      ta += sa[j];
-      tb += sb[j];
-    }
-    if (ta | tb) {
-      atomicAdd(&global[0], ta);
-      atomicAdd(&global[1], tb);
+struct BlockTotals {
+  unsigned long long sums[2];
+  uint32_t waves;
+
+  // Before a barrier that every wave passes.
+  __device__ __forceinline__ void clear() {
+    if (threadIdx.x == 0u) {
+      sums[0] = sums[1] = 0u;
+      waves = 0u;
     }
   }
-}
+
+  // Called once by every lane of every wave.
+  __device__ __forceinline__ void publish(unsigned long long *global, unsigned long long a,
+                                          unsigned long long b) {
+    a = wave_sum_u64(a);
+    b = wave_sum_u64(b);
+    const uint32_t lane = threadIdx.x & 63u;
+    uint32_t before = 0u;
+    if (lane < 2u) atomicAdd(&sums[lane], lane == 0u ? a : b);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    if (lane == 0u) before = atomicAdd(&waves, 1u);
+    before = __builtin_amdgcn_readfirstlane(before);
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup");
+    if (before + 1u == uint32_t(kBlockThreads / 64) && lane < 2u) {
+      const unsigned long long t = atomicAdd(&sums[lane], 0ull);
+      if (t) atomicAdd(&global[lane], t);
+    }
+  }
+};
 
 // Random actions.  The actions of a 64-environment block at one step are
 // one generator output (see action_bit); every 64 steps each lane computes
@@ -235,6 +247,11 @@ template <Traj kTraj, class Policy, class P = PrecF32>
 __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy &policy) {
   using T = typename P::T;
   using S = typename P::S;
+  __shared__ BlockTotals<kResidentBlock> totals;
+  if (p.global) {
+    totals.clear();
+    __syncthreads();
+  }
   T *const px = reinterpret_cast<T *>(p.x);
   T *const pxd = reinterpret_cast<T *>(p.xd);
   T *const pth = reinterpret_cast<T *>(p.th);
@@ -406,7 +423,7 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     }
     if (p.ret_sum) p.ret_sum[i] = (p.first ? 0u : p.ret_sum[i]) + returns;
   }
-  if (p.global) block_publish<kResidentBlock>(p.global, n_done, valid ? returns : 0u, false);
+  if (p.global) totals.publish(p.global, n_done, valid ? returns : 0u);
 }
 
 }  // namespace cp

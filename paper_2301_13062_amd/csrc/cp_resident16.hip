@@ -292,6 +292,8 @@ template <bool kTraj>
 __global__ __launch_bounds__(kBlock16) void k_resident_f16x2(RolloutParams p) {
   __shared__ uint32_t lut[kLutWords];
   __shared__ uint32_t xch[kWaves16][64][2];  // each wave's refill exchange
+  __shared__ BlockTotals<kBlock16> totals;
+  totals.clear();
   for (uint32_t b = threadIdx.x; b < kLutWords; b += kBlock16)
     lut[b] = b < kRecipCosWord                   ? __builtin_bit_cast(uint32_t, kRecipDen16.v[b - kDenWord])
              : b < kAngleWord                    ? __builtin_bit_cast(uint32_t, kRecipCos16.v[b - kRecipCosWord])
@@ -491,7 +493,7 @@ __global__ __launch_bounds__(kBlock16) void k_resident_f16x2(RolloutParams p) {
       if (p.ret_sum) p.ret_sum[i] = (p.first ? 0u : p.ret_sum[i]) + ret;
     }
   }
-  if (p.global) block_publish<kBlock16>(p.global, n_done_lane, returns, false);
+  if (p.global) totals.publish(p.global, n_done_lane, returns);
 }
 
 }  // namespace
