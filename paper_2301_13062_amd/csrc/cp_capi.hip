@@ -423,6 +423,8 @@ int run_rollout(cp_states *s, int64_t n_steps, uint64_t seed, const cp_traj &tr,
     for (int64_t j = 0; j < n_steps && !replayed; ++j) {
       p.t = uint32_t(s->t + uint64_t(j));
       p.first = j == 0;
+      p.last = j + 1 == n_steps;
+      p.steps = uint32_t(n_steps);
       p.obs = tr.obs ? tr.obs + size_t(j) * 4u * n : nullptr;
       p.reward = tr.reward ? tr.reward + size_t(j) * n : nullptr;
       p.done = tr.done ? tr.done + size_t(j) * n : nullptr;

@@ -24,10 +24,11 @@ struct StepParams {
   float *obs;              // [4][n] or nullptr
   float *reward;           // [n] or nullptr
   uint8_t *done;           // [n] or nullptr
-  uint32_t *done_count;    // [n] rollout accumulators, or nullptr
+  uint32_t *done_count;    // [n] rollout statistics, or nullptr
   float *total_reward;
   uint32_t *ret_sum;
-  uint32_t first;          // 1: accumulators start from zero at this step
+  uint32_t first, last;    // 1: the first, the last step of a rollout (statistics)
+  uint32_t steps;          // steps of the rollout (read where last is 1)
 };
 
 // A whole rollout of T steps in one launch (register-resident).
