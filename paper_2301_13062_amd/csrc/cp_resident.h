@@ -108,7 +108,9 @@ struct BlockTotals {
 // two blocks and computes both.
 template <bool kAligned>
 struct HashPolicy {
-  static constexpr bool kUnrolled = true;  // the rounds of kRefill steps
+  static constexpr bool kUnrolled = true;      // the rounds of kRefill steps
+  static constexpr bool kBlockRefill = true;   // refills of the trajectory form
+  static constexpr uint32_t kEnvsPerWave = 64;
   U2 key;
   uint32_t env, g0;
   U2 b0, b1;  // this lane's blocks for step (t & ~63) + lane
@@ -227,6 +229,15 @@ __device__ __forceinline__ void each_of(F &f, std::integer_sequence<int, r...>) 
   (f(std::integral_constant<int, r>{}), ...);
 }
 
+// The lane's environment of a launch: kEnvsPerWave consecutive ones per wave;
+// with fewer than 64 the lanes past them run the first ones' again (the same
+// values) and store nothing.
+template <class Policy>
+__device__ __forceinline__ uint32_t lane_env() {
+  constexpr uint32_t kEnvs = Policy::kEnvsPerWave;
+  return (blockIdx.x * kResidentWaves + (threadIdx.x >> 6)) * kEnvs + (threadIdx.x & (kEnvs - 1u));
+}
+
 // The loop.  `policy(t, s)` returns the action of step t for the lane's
 // pre-step state s; it is called by every lane of the wave at every step
 // (policies may use cross-lane operations).  P is the precision of the
@@ -256,9 +267,9 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   T *const pxd = reinterpret_cast<T *>(p.xd);
   T *const pth = reinterpret_cast<T *>(p.th);
   T *const pthd = reinterpret_cast<T *>(p.thd);
-  const uint32_t i = blockIdx.x * kResidentBlock + threadIdx.x;
+  const uint32_t i = lane_env<Policy>();
   const bool off32 = uint64_t(p.n) * (sizeof(T) > 4 ? sizeof(T) : 4) <= (uint64_t(1) << 32);
-  const bool valid = i < p.n;
+  const bool valid = i < p.n, owner = valid && (threadIdx.x & 63u) < Policy::kEnvsPerWave;
   const uint32_t env = p.env_base + i;
   // Lanes past the end run the loop on a NaN state (the wave stays converged
   // for the cross-lane operations): it never terminates.  They store nothing.
@@ -292,7 +303,7 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     used |= m;
     s = o;
     if constexpr (kTraj != Traj::kNone) {
-      if (valid) {
+      if (owner) {
         if (kTraj == Traj::kAll || off32)
           store_traj<kTraj == Traj::kAll, true>(row_obs, row_reward, row_done, p.n, i, s, d);
         else
@@ -361,7 +372,7 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     if (mine) nxt = got[slot];
   };
   auto refill = [&](uint32_t j) {
-    if constexpr (kTraj != Traj::kNone) refill_block(j);
+    if constexpr (kTraj != Traj::kNone && Policy::kBlockRefill) refill_block(j);
     else refill_wave(j);
   };
   // The launch's first step (any state), single steps up to a multiple of
@@ -405,7 +416,7 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   const uint32_t len = k != k0 ? p.T - 1u - last : len0 + p.T;
   const uint32_t n_done = k - k0;
   const uint32_t returns = p.T + len0 - len;
-  if (valid) {
+  if (owner) {
     px[i] = s.x;
     pxd[i] = s.xd;
     pth[i] = s.th;
@@ -423,7 +434,7 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     }
     if (p.ret_sum) p.ret_sum[i] = (p.first ? 0u : p.ret_sum[i]) + returns;
   }
-  if (p.global) totals.publish(p.global, n_done, valid ? returns : 0u);
+  if (p.global) totals.publish(p.global, owner ? n_done : 0u, owner ? returns : 0u);
 }
 
 }  // namespace cp
