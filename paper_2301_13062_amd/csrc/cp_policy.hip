@@ -402,7 +402,7 @@ static void policy_as(const RolloutParams &p, hipStream_t stream) {
     case Traj::kAny:
       hipLaunchKernelGGL((k_resident_policy<Traj::kAny, kTiles>), grid, b, 0, stream, p);
       break;
-    case Traj::kAll:
+    default:
       hipLaunchKernelGGL((k_resident_policy<Traj::kAll, kTiles>), grid, b, 0, stream, p);
       break;
   }

@@ -61,7 +61,7 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 // wave that counts last publishes them (lanes 0 and 1 one sum each).  No
 // barrier: waves end at different times, and ended ones leave their issue
 // slots to the others, where waves waiting at a barrier slowed the rest
-// (1,048,576 x 1,000 in binary16 1,375 -> 1,2xx us).
+// (1,048,576 x 1,000 in binary16 1,375 -> 1,250 us).
 // Atomics on one line come back at about 10 ns each however many blocks
 // issue them (65,536 blocks adding their two sums one after the other cost
 // a 230 us launch another 1.34 ms), so kernels whose blocks are short call it
@@ -150,13 +150,31 @@ struct HashPolicy {
 
 // What a launch stores per step: nothing, whichever of obs [T][4][n] (in the
 // state's type), reward [T][n] f32 and done [T][n] u8 are given, or all three
-// with every byte offset within a plane below 2^32 (no tests in the loop).
-enum class Traj { kNone, kAny, kAll };
+// with every byte offset within a plane below 2^32 (no tests in the loop), each
+// wave its own environments (kAll) or the block its piece of a row (kRows).
+enum class Traj { kNone, kAny, kAll, kRows };
 
 inline Traj traj_kind(const RolloutParams &p, size_t elem) {
   if (!p.obs && !p.reward && !p.done) return Traj::kNone;
   const bool off32 = uint64_t(p.n) * (elem > 4 ? elem : 4) <= (uint64_t(1) << 32);
   return p.obs && p.reward && p.done && off32 ? Traj::kAll : Traj::kAny;
+}
+
+// Whether a launch stores by rows (Traj::kRows): rows that start off the
+// 128-byte lines, in a trajectory that the 256 MB memory-side cache does not
+// absorb (as it does up to there: 200,003 x 64 in binary32, 269 MB: 55 us by
+// waves, 75 by rows; 300,007 x 64, 403 MB: 119 and 105).  Blocks of 1,024, and
+// below kRowsWideMinEnvs, where those leave CUs idle or with twice the work of
+// others, of 512 (300,007 x 64: 146 and 105 us; 500,009: 152 and 168).  The
+// flags' rows do not count (4,194,240 x 64: 1,189 us by waves, 1,180 by rows).
+constexpr uint64_t kRowsMinBytes = uint64_t(384) << 20;
+constexpr uint32_t kRowsWideMinEnvs = 400000;
+
+inline bool by_rows(const RolloutParams &p, size_t elem) {
+  const uintptr_t starts = reinterpret_cast<uintptr_t>(p.obs) | reinterpret_cast<uintptr_t>(p.reward) |
+                           uintptr_t(p.n * uint64_t(elem < 4 ? elem : 4));
+  return traj_kind(p, elem) == Traj::kAll && starts % 128u != 0u &&
+         uint64_t(p.n) * p.T * (4u * elem + 5u) >= kRowsMinBytes;
 }
 
 // Stores of one step (obs, reward and done: the step's rows).  Each plane's
@@ -238,6 +256,39 @@ __device__ __forceinline__ uint32_t lane_env() {
   return (blockIdx.x * kResidentWaves + (threadIdx.x >> 6)) * kEnvs + (threadIdx.x & (kEnvs - 1u));
 }
 
+// The block's place in the batch, blocks of one XCD (every eighth is launched
+// on the same one) next to each other.
+__device__ __forceinline__ uint32_t xcd_block() {
+  const uint32_t x = blockIdx.x & 7u, q = gridDim.x >> 3, r = gridDim.x & 7u;
+  return x * q + (x < r ? x : r) + (blockIdx.x >> 3);
+}
+
+// Whole rows by block (kRows), for trajectories whose rows do not all start on
+// a 128-byte line.  Waves that store their own 64 values each then leave parts
+// of two lines, completed by another wave at another time -- mostly after
+// the part was written out, which costs a multiple of a whole line.  So
+// the block puts a step's values into LDS and stores its piece of each row
+// from the row's own first line boundary on (`turned`): all lines but the two
+// at the piece's ends are written whole by one instruction, and the blocks
+// of one XCD lie next to each other, so that most end lines too are completed
+// in the same L2.  4,194,303 x 64 in binary32: 2,127 us stored by waves,
+// 1,700 by blocks of 256 on consecutive places, 1,850 by blocks of 1,024 as
+// launched, 1,196 by those on consecutive places (aligned rows: 1,109); in
+// binary64 3,258 -> 1,949.
+template <class T, int kBlockThreads>
+struct RowStage {
+  T v[4][kBlockThreads];
+  uint8_t done[kBlockThreads];
+};
+
+// The lane's element of the block's piece of a row: the elements from the
+// first 128-byte line on come first, those before it last.
+template <int kBlockThreads>
+__device__ __forceinline__ uint32_t turned(const void *piece, uint32_t elem_bytes) {
+  const uint32_t head = (0u - uint32_t(reinterpret_cast<uintptr_t>(piece))) & 127u;
+  return (threadIdx.x + head / elem_bytes) & uint32_t(kBlockThreads - 1);
+}
+
 // The loop.  `policy(t, s)` returns the action of step t for the lane's
 // pre-step state s; it is called by every lane of the wave at every step
 // (policies may use cross-lane operations).  P is the precision of the
@@ -254,11 +305,12 @@ __device__ __forceinline__ uint32_t lane_env() {
 // selects, a second termination tested for at every step): 1,048,576 x 1,000
 // in binary32 1.293 -> 1.227 ms, in binary64 2.54 -> 2.04 ms; 1,024 x 200,
 // where a step costs one wave's instruction stream, 41.8 -> 33.4 us.
-template <Traj kTraj, class Policy, class P = PrecF32>
+template <Traj kTraj, class Policy, class P = PrecF32, int kBlockThreads = kResidentBlock>
 __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy &policy) {
   using T = typename P::T;
   using S = typename P::S;
-  __shared__ BlockTotals<kResidentBlock> totals;
+  constexpr int kWaves = kBlockThreads / 64;
+  __shared__ BlockTotals<kBlockThreads> totals;
   if (p.global) {
     totals.clear();
     __syncthreads();
@@ -267,7 +319,8 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   T *const pxd = reinterpret_cast<T *>(p.xd);
   T *const pth = reinterpret_cast<T *>(p.th);
   T *const pthd = reinterpret_cast<T *>(p.thd);
-  const uint32_t i = lane_env<Policy>();
+  const uint32_t piece0 = xcd_block() * uint32_t(kBlockThreads);  // kRows: the block's first one
+  const uint32_t i = kTraj == Traj::kRows ? piece0 + threadIdx.x : lane_env<Policy>();
   const bool off32 = uint64_t(p.n) * (sizeof(T) > 4 ? sizeof(T) : 4) <= (uint64_t(1) << 32);
   const bool valid = i < p.n, owner = valid && (threadIdx.x & 63u) < Policy::kEnvsPerWave;
   const uint32_t env = p.env_base + i;
@@ -291,6 +344,34 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   T *row_obs = reinterpret_cast<T *>(p.obs);
   float *row_reward = p.reward;
   uint8_t *row_done = p.done;
+  // The block's piece of the step's rows, through LDS (two stages in turn, so
+  // that one barrier per step orders a stage's readers before its next
+  // writers).
+  uint32_t turn = 0u;
+  const bool whole = piece0 + uint32_t(kBlockThreads) <= p.n;
+  auto store_rows = [&](bool d) {
+    __shared__ RowStage<T, kBlockThreads> stages[2];
+    RowStage<T, kBlockThreads> &st = stages[turn];
+    turn ^= 1u;
+    st.v[0][threadIdx.x] = s.x;
+    st.v[1][threadIdx.x] = s.xd;
+    st.v[2][threadIdx.x] = s.th;
+    st.v[3][threadIdx.x] = s.thd;
+    st.done[threadIdx.x] = uint8_t(d);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t c = 0; c < 4u; ++c) {
+      T *const piece = row_obs + size_t(c) * p.n + piece0;
+      const uint32_t e = turned<kBlockThreads>(piece, sizeof(T));
+      if (whole || piece0 + e < p.n) *elem<true>(piece, e) = st.v[c][e];
+    }
+    float *const piece_r = row_reward + piece0;
+    const uint32_t er = turned<kBlockThreads>(piece_r, sizeof(float));
+    if (whole || piece0 + er < p.n) *elem<true>(piece_r, er) = 1.0f;
+    uint8_t *const piece_d = row_done + piece0;
+    const uint32_t ed = turned<kBlockThreads>(piece_d, 1u);
+    if (whole || piece0 + ed < p.n) *elem<true>(piece_d, ed) = st.done[ed];
+  };
   // One step at global index t, the r-th after the last refill; `limited`:
   // the state is one a step produced (every step after a launch's first), its
   // angle within the limit or NaN.
@@ -302,16 +383,20 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     take(m, o, nxt, lr, r);
     used |= m;
     s = o;
-    if constexpr (kTraj != Traj::kNone) {
+    if constexpr (kTraj == Traj::kRows) {
+      store_rows(d);
+    } else if constexpr (kTraj != Traj::kNone) {
       if (owner) {
         if (kTraj == Traj::kAll || off32)
           store_traj<kTraj == Traj::kAll, true>(row_obs, row_reward, row_done, p.n, i, s, d);
         else
           store_traj<false, false>(row_obs, row_reward, row_done, p.n, i, s, d);
       }
-      if (kTraj == Traj::kAll || row_obs) row_obs += 4u * size_t(p.n);
-      if (kTraj == Traj::kAll || row_reward) row_reward += p.n;
-      if (kTraj == Traj::kAll || row_done) row_done += p.n;
+    }
+    if constexpr (kTraj != Traj::kNone) {
+      if (kTraj >= Traj::kAll || row_obs) row_obs += 4u * size_t(p.n);
+      if (kTraj >= Traj::kAll || row_reward) row_reward += p.n;
+      if (kTraj >= Traj::kAll || row_done) row_done += p.n;
     }
   };
   // After the steps from the j-th of this launch on: the lanes that ended an
@@ -343,16 +428,16 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   // are never overwritten while a wave may still read them.
   uint32_t parity = 0u;
   auto refill_block = [&](uint32_t j) {
-    __shared__ uint32_t wave_cnt[2][kResidentWaves];
-    __shared__ uint32_t req_env[kResidentBlock], req_k[kResidentBlock];
-    __shared__ S got[kResidentBlock];
+    __shared__ uint32_t wave_cnt[2][kWaves];
+    __shared__ uint32_t req_env[kBlockThreads], req_k[kBlockThreads];
+    __shared__ S got[kBlockThreads];
     const uint32_t wave = threadIdx.x >> 6;
     const unsigned long long m = used;
     if ((threadIdx.x & 63u) == 0u) wave_cnt[parity][wave] = uint32_t(__popcll(m));
     __syncthreads();
     uint32_t base = 0u, total = 0u;
 #pragma unroll
-    for (uint32_t v = 0; v < uint32_t(kResidentWaves); ++v) {
+    for (uint32_t v = 0; v < uint32_t(kWaves); ++v) {
       const uint32_t c = wave_cnt[parity][v];
       base += v < wave ? c : 0u;
       total += c;
@@ -395,7 +480,7 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   for (; j + kRefill <= p.T; j += kRefill) {
     const uint32_t t = p.t0 + j;
     policy.prepare(t, false);
-    if constexpr (Policy::kUnrolled) {
+    if constexpr (Policy::kUnrolled && kTraj != Traj::kRows) {
       auto one = [&](auto r) { step(t + uint32_t(decltype(r)::value), r, limited_angle{}); };
       each_of(one, std::make_integer_sequence<int, int(kRefill)>{});
     } else {

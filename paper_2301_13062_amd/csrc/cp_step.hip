@@ -208,8 +208,9 @@ __device__ __forceinline__ void fused_one(const StepParams &p, uint32_t i, uint3
 // a carried length (measured 123.4 -> 113.0 us per launch).
 enum class Phase { kFirst, kMid, kLast };
 
-// One environment's step; n_done and ret: the last step's totals.
-template <Phase kPhase, bool kOff32>
+// One environment's step; n_done and ret: the last step's totals.  kRowBlock:
+// the threads of a block that stores its pieces of the rows together, or 0.
+template <Phase kPhase, bool kOff32, int kRowBlock>
 __device__ __forceinline__ void stream_one(const StepParams &p, uint32_t i, uint32_t j, uint32_t T,
                                            uint32_t &n_done, uint32_t &ret) {
   // The middle and last steps below 2^30 environments load the state (and
@@ -230,6 +231,8 @@ __device__ __forceinline__ void stream_one(const StepParams &p, uint32_t i, uint
   }
   const uint32_t a = action_bit_wave(p.kact, p.env_base + i, p.t);
   n_done = ret = 0u;
+  State o{0.0f, 0.0f, 0.0f, 0.0f};
+  uint32_t d = 0u;
   if (i < p.n) {
     if (!kEarly) {
       s = State{__builtin_nontemporal_load(elem<kOff32>(p.xi, i)),
@@ -249,8 +252,8 @@ __device__ __forceinline__ void stream_one(const StepParams &p, uint32_t i, uint
       *elem<kOff32>(p.x, i) = __builtin_bit_cast(float, k0);
       *elem<kOff32>(p.xd, i) = __builtin_bit_cast(float, len0);
     }
-    State o = dynamics(s, force_of(a));
-    const uint32_t d = terminated(o) ? 1u : 0u;
+    o = dynamics(s, force_of(a));
+    d = terminated(o) ? 1u : 0u;
     if (kOff32 && kPhase != Phase::kLast) {
       // The counters as buffer accesses whose offset lies past the end of
       // the arrays on the lanes that do not terminate (such a lane reads 0
@@ -279,7 +282,9 @@ __device__ __forceinline__ void stream_one(const StepParams &p, uint32_t i, uint
       }
       o = reset_draw(p.krst, p.env_base + i, k);
     }
-    if (kOff32) {
+    if (kRowBlock != 0) {
+      // the block's rows, below
+    } else if (kOff32) {
       // the trajectory's write streams as buffer stores with the nt and sc1
       // cache bits (2% faster than nt alone for these streams, measured)
       const uint32_t pb = p.n * 4u;  // below 2^32: n < 2^30 here
@@ -324,6 +329,32 @@ __device__ __forceinline__ void stream_one(const StepParams &p, uint32_t i, uint
       if (p.ret_sum) *elem<kOff32>(p.ret_sum, i) = ret;
     }
   }
+  if constexpr (kRowBlock != 0) {
+    // the block's piece of each row (cp_resident.h, kRows); a lane whose
+    // element is past the end of the row writes nothing
+    __shared__ RowStage<float, kRowBlock> st;
+    const uint32_t tid = threadIdx.x, piece0 = i - tid, pb = p.n * 4u;
+    st.v[0][tid] = o.x;
+    st.v[1][tid] = o.xd;
+    st.v[2][tid] = o.th;
+    st.v[3][tid] = o.thd;
+    st.done[tid] = uint8_t(d);
+    __syncthreads();
+#pragma unroll
+    for (uint32_t c = 0; c < 4u; ++c) {
+      float *const row = p.obs + size_t(c) * p.n;
+      const uint32_t e = turned<kRowBlock>(row + piece0, 4u);
+      stream_store(st.v[c][e], plane_rsrc(row, pb), int((piece0 + e) * 4u));
+    }
+    if (p.reward)
+      stream_store(1.0f, plane_rsrc(p.reward, pb),
+                   int((piece0 + turned<kRowBlock>(p.reward + piece0, 4u)) * 4u));
+    if (p.done) {
+      const uint32_t e = turned<kRowBlock>(p.done + piece0, 1u);
+      __builtin_amdgcn_raw_buffer_store_b8(st.done[e], plane_rsrc(p.done, p.n), int(piece0 + e), 0,
+                                           kStreamAux);
+    }
+  }
 }
 
 // Blocks of a last step that adds to the totals: eight 256-lane blocks per
@@ -332,12 +363,29 @@ __device__ __forceinline__ void stream_one(const StepParams &p, uint32_t i, uint
 // environments 1,590 -> 310 us).
 constexpr uint32_t kTotalsBlocks = 2048;
 
+// The first and middle steps below 2^30 environments where the rows do not
+// start on 128-byte lines: each block's pieces of the rows through LDS.  Parts
+// of lines cost these write-through stores most: 16,777,213 x 32 with the
+// trajectory 6,684 us stored by waves, 4,786 by rows in blocks of 256, 4,944
+// of 512, 5,034 of 1,024; 8,000,002 x 16: 1,559, 1,247, 1,181, 1,260;
+// 2,097,153 x 16: 483, 401, 391, 399 (blocks of 512 on consecutive places of
+// one XCD: 4,700, 1,275, 381).  Aligned rows: 16,777,216 x 32 3,792 by waves,
+// 3,939 at best by rows.
+constexpr int kStreamRowBlock = 512;
+
+template <Phase kPhase>
+__global__ __launch_bounds__(kStreamRowBlock) void k_stream_rows(StepParams p, uint32_t j, uint32_t T) {
+  uint32_t n_done, ret;
+  stream_one<kPhase, true, kStreamRowBlock>(p, blockIdx.x * kStreamRowBlock + threadIdx.x, j, T,
+                                            n_done, ret);
+}
+
 template <Phase kPhase, bool kOff32>
 __global__ __launch_bounds__(kBlock) void k_stream_step(StepParams p, uint32_t j, uint32_t T,
                                                         unsigned long long *global) {
   uint32_t n_done, ret;
   if (kPhase != Phase::kLast) {
-    stream_one<kPhase, kOff32>(p, blockIdx.x * kBlock + threadIdx.x, j, T, n_done, ret);
+    stream_one<kPhase, kOff32, 0>(p, blockIdx.x * kBlock + threadIdx.x, j, T, n_done, ret);
     return;
   }
   __shared__ BlockTotals<kBlock> totals;
@@ -345,7 +393,7 @@ __global__ __launch_bounds__(kBlock) void k_stream_step(StepParams p, uint32_t j
   __syncthreads();
   unsigned long long all_done = 0u, all_ret = 0u;
   for (uint32_t base = blockIdx.x * kBlock; base < p.n; base += gridDim.x * kBlock) {
-    stream_one<kPhase, kOff32>(p, base + threadIdx.x, j, T, n_done, ret);
+    stream_one<kPhase, kOff32, 0>(p, base + threadIdx.x, j, T, n_done, ret);
     all_done += n_done;
     all_ret += ret;
   }
@@ -603,10 +651,11 @@ hipError_t rollout_graph(const RolloutKey &k, RolloutGraph **out) {
   return hipSuccess;
 }
 
-template <Traj kTraj, class P, bool kAligned>
-__global__ __launch_bounds__(kResidentBlock) void k_resident(RolloutParams p) {
-  HashPolicy<kAligned> policy(p.kact, p.env_base + blockIdx.x * kResidentBlock + threadIdx.x);
-  resident_rollout<kTraj, HashPolicy<kAligned>, P>(p, policy);
+template <Traj kTraj, class P, bool kAligned, int kBlockThreads = kResidentBlock>
+__global__ __launch_bounds__(kBlockThreads) void k_resident(RolloutParams p) {
+  const uint32_t block = kTraj == Traj::kRows ? xcd_block() : blockIdx.x;
+  HashPolicy<kAligned> policy(p.kact, p.env_base + block * kBlockThreads + threadIdx.x);
+  resident_rollout<kTraj, HashPolicy<kAligned>, P, kBlockThreads>(p, policy);
 }
 
 // Totals of a per-step rollout from the episode counters: over T steps an
@@ -682,6 +731,15 @@ static void stream_as(const StepParams &p, uint32_t j, uint32_t T,
                       unsigned long long *global, hipStream_t stream) {
   dim3 g = grid_for(p.n);
   const dim3 b(kBlock);
+  if constexpr (kPhase != Phase::kLast) {
+    const uintptr_t starts = reinterpret_cast<uintptr_t>(p.obs) | reinterpret_cast<uintptr_t>(p.reward) |
+                             uintptr_t(p.n) * 4u;
+    if (starts % 128u != 0u && p.n < kOff32MaxEnvs) {
+      hipLaunchKernelGGL(k_stream_rows<kPhase>, dim3((p.n + kStreamRowBlock - 1) / kStreamRowBlock),
+                         dim3(kStreamRowBlock), 0, stream, p, j, T);
+      return;
+    }
+  }
   if (kPhase == Phase::kLast && global && g.x > kTotalsBlocks) g.x = kTotalsBlocks;
   if (p.n < kOff32MaxEnvs)
     hipLaunchKernelGGL((k_stream_step<kPhase, true>), g, b, 0, stream, p, j, T, global);
@@ -756,8 +814,21 @@ hipError_t launch_concat_step(const StepParams &p, void *workspace, hipStream_t 
   return hipGetLastError();
 }
 
+template <class P, bool kAligned, int kBlockThreads>
+static void resident_rows_as(const RolloutParams &p, hipStream_t stream) {
+  hipLaunchKernelGGL((k_resident<Traj::kRows, P, kAligned, kBlockThreads>),
+                     dim3((p.n + kBlockThreads - 1) / kBlockThreads), dim3(kBlockThreads), 0, stream, p);
+}
+
 template <class P, bool kAligned>
 static void resident_as(const RolloutParams &p, hipStream_t stream) {
+  if constexpr (!std::is_same_v<P, PrecF16>) {
+    if (by_rows(p, sizeof(typename P::T))) {
+      if (p.n < kRowsWideMinEnvs) resident_rows_as<P, kAligned, 512>(p, stream);
+      else resident_rows_as<P, kAligned, 1024>(p, stream);
+      return;
+    }
+  }
   const dim3 grid((p.n + kResidentBlock - 1) / kResidentBlock), b(kResidentBlock);
   switch (traj_kind(p, sizeof(typename P::T))) {
     case Traj::kNone:
@@ -766,7 +837,7 @@ static void resident_as(const RolloutParams &p, hipStream_t stream) {
     case Traj::kAny:
       hipLaunchKernelGGL((k_resident<Traj::kAny, P, kAligned>), grid, b, 0, stream, p);
       break;
-    case Traj::kAll:
+    default:
       hipLaunchKernelGGL((k_resident<Traj::kAll, P, kAligned>), grid, b, 0, stream, p);
       break;
   }
