@@ -195,6 +195,7 @@ struct MlpPolicy {
   // instruction cache
   static constexpr bool kUnrolled = false;
   static constexpr bool kBlockRefill = false;  // bound by the network, not by stores
+  static constexpr bool kAhead = false;
   static constexpr uint32_t kEnvsPerWave = 16u * kTiles;
   static constexpr int kPair = kTiles > 1 ? 2 : 1;  // tiles in flight
   // One tile per wave (at most three waves per SIMD): all of layer 2's row
@@ -312,15 +313,15 @@ struct MlpPolicy {
     return right;
   }
 
-  // Action of the lane's environment for its pre-step state s.  Called by
+  // Action of the lane's environment for its pre-step state s, in the top bit.  Called by
   // every lane of the wave.  The clamp is a half-rate instruction, a seventh
   // of a tanh's issue time; every wave of the usual networks and states goes
   // without (4,194,304 x 64: 11.06 -> 10.32 ms).
-  __device__ __forceinline__ uint32_t operator()(uint32_t, const State &s) const {
+  __device__ __forceinline__ uint32_t operator()(const State &s) const {
     const float sum = (__builtin_fabsf(s.x) + __builtin_fabsf(s.xd)) +
                       (__builtin_fabsf(s.th) + __builtin_fabsf(s.thd));
     const unsigned long long right = __all(sum <= free_sum || past) ? evaluate<false>(s) : evaluate<true>(s);
-    return __builtin_amdgcn_inverse_ballot_w64(right) ? 1u : 0u;
+    return __builtin_amdgcn_inverse_ballot_w64(right) ? 0x80000000u : 0u;
   }
 };
 
@@ -355,8 +356,8 @@ __global__ __launch_bounds__(kResidentBlock, kTiles == 1 ? 2 : 1) void k_policy_
     // plane offsets in 64 bits: 3n passes 2^32 from n > 1,431,655,765
     const size_t m = n;
     const State s{obs[ic], obs[m + ic], obs[2u * m + ic], obs[3u * m + ic]};
-    const uint32_t a = policy(0u, s);
-    if (owner && i < n) actions[i] = uint8_t(a);
+    const uint32_t a = policy(s);
+    if (owner && i < n) actions[i] = uint8_t(a >> 31);
   }
 }
 

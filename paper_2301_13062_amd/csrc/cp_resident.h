@@ -98,53 +98,105 @@ struct BlockTotals {
   }
 };
 
-// Random actions.  The actions of a 64-environment block at one step are
-// one generator output (see action_bit); every 64 steps each lane computes
-// the block of one of the next 64 steps (lane L: step base + L), and each
-// step reads its block from the owning lane (v_readlane) into scalar
-// registers.  Waves start at multiples of 64 environments after the
-// launch's first one, so either every wave is aligned to a block
-// (kAligned: the launch starts at a multiple of 64) or every wave straddles
-// two blocks and computes both.
+// The value of lane (this lane ^ kMask), within rows of 16 lanes.
+template <int kMask>
+__device__ __forceinline__ uint32_t lane_xor(uint32_t v) {
+  const int x = int(v);
+  if (kMask == 1) return uint32_t(__builtin_amdgcn_mov_dpp(x, 0xB1, 0xF, 0xF, true));  // quad_perm 1,0,3,2
+  if (kMask == 2) return uint32_t(__builtin_amdgcn_mov_dpp(x, 0x4E, 0xF, 0xF, true));  // quad_perm 2,3,0,1
+  if (kMask == 8) return uint32_t(__builtin_amdgcn_mov_dpp(x, 0x128, 0xF, 0xF, true));  // row_ror:8
+  static_assert(kMask == 1 || kMask == 2 || kMask == 4 || kMask == 8, "a bit of a row's lane");
+  const int m = __builtin_amdgcn_mov_dpp(x, 0x141, 0xF, 0xF, true);  // row_half_mirror: ^ 7
+  return uint32_t(__builtin_amdgcn_mov_dpp(m, 0x1B, 0xF, 0xF, true));  // quad_perm 3,2,1,0: ^ 3
+}
+
+// One stage of the transposition below: bits whose index has bit kS set (or
+// clear, in a lane with that bit) come from the lane ^ kS.
+template <int kS>
+__device__ __forceinline__ uint32_t transpose_stage(uint32_t x, uint32_t lane) {
+  constexpr uint32_t kLow = kS == 8 ? 0x00FF00FFu : kS == 4 ? 0x0F0F0F0Fu : kS == 2 ? 0x33333333u : 0x55555555u;
+  const bool high = (lane & uint32_t(kS)) != 0u;
+  const uint32_t keep = high ? ~kLow : kLow, y = lane_xor<kS>(x);
+  const uint32_t r = __builtin_amdgcn_alignbit(y, y, high ? kS : 32 - kS);
+  return (x & keep) | (r & ~keep);
+}
+
+// The 64 x 64 bit matrix whose row L is lane L's (a, b), a the columns 0 to
+// 31, transposed: bit i of lane L's a' is row i's column L, of b' row i + 32's.
+__device__ __forceinline__ void transpose64(uint32_t &a, uint32_t &b) {
+  const uint32_t lane = threadIdx.x & 63u;
+  auto s32 = __builtin_amdgcn_permlane32_swap(a, b, false, false);
+  a = s32[0];
+  b = s32[1];
+  auto half = [&](uint32_t x) {
+    // even rows of 16 lanes: both rows' low halves; odd ones: the high halves
+    auto s16 = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    x = __builtin_amdgcn_perm(s16[1], s16[0], (lane & 16u) ? 0x07060302u : 0x05040100u);
+    x = transpose_stage<8>(x, lane);
+    x = transpose_stage<4>(x, lane);
+    x = transpose_stage<2>(x, lane);
+    return transpose_stage<1>(x, lane);
+  };
+  a = half(a);
+  b = half(b);
+}
+
+// Random actions.  The actions of a 64-environment block at one step are one
+// generator output (see action_bit).  Every 64 steps each lane computes the
+// wave's output of one of the next 64 steps, and the wave transposes them, so
+// that each lane holds its environment's actions of these steps as two words,
+// the first step in the top bit: a step's action is the word's top bit and a
+// shift (two full-rate instructions, where reading the step's output from the
+// owning lane and selecting by it took five at half rate).  Waves start at
+// multiples of 64 environments after the launch's first one, so either every
+// wave is aligned to a block (kAligned: the launch starts at a multiple of 64)
+// or every wave straddles two blocks and computes both.
 template <bool kAligned>
 struct HashPolicy {
   static constexpr bool kUnrolled = true;      // the rounds of kRefill steps
   static constexpr bool kBlockRefill = true;   // refills of the trajectory form
+  static constexpr bool kAhead = true;         // more than one start state ahead
   static constexpr uint32_t kEnvsPerWave = 64;
   U2 key;
-  uint32_t env, g0;
-  U2 b0, b1;  // this lane's blocks for step (t & ~63) + lane
+  uint32_t g0, off;  // the wave's first block and place in it
+  uint32_t word, later;  // this lane's actions from the next step on; of steps 32 .. 63
 
-  __device__ __forceinline__ HashPolicy(U2 k, uint32_t e) : key(k), env(e) {
-    g0 = uint32_t(__builtin_amdgcn_readfirstlane(int(e))) >> 6;  // logical shift: e may be >= 2^31
+  __device__ __forceinline__ HashPolicy(U2 k, uint32_t env) : key(k) {
+    const uint32_t first = uint32_t(__builtin_amdgcn_readfirstlane(int(env)));
+    g0 = first >> 6;
+    off = first & 63u;
   }
 
   // Called before the first step of a launch and before the steps whose
   // index is a multiple of kRefill.
   __device__ __forceinline__ void prepare(uint32_t t, bool first) {
-    if (!first && (t & 63u) != 0u) return;
-    const uint32_t step = (t & ~63u) + (threadIdx.x & 63u);
-    b0 = threefry2x32(key.a, key.b, g0, step);
-    if (!kAligned) b1 = threefry2x32(key.a, key.b, g0 + 1u, step);
+    if (!first && (t & 31u) != 0u) return;
+    if (!first && (t & 63u) != 0u) {
+      word = later;
+      return;
+    }
+    // rows in descending order of their steps within each half
+    const uint32_t step = (t & ~63u) + ((threadIdx.x & 63u) ^ 31u);
+    U2 w = threefry2x32(key.a, key.b, g0, step);
+    if (!kAligned) {
+      const U2 w1 = threefry2x32(key.a, key.b, g0 + 1u, step);
+      const unsigned long long lo = (static_cast<unsigned long long>(w.b) << 32) | w.a;
+      const unsigned long long hi = (static_cast<unsigned long long>(w1.b) << 32) | w1.a;
+      const unsigned long long both = off == 0u ? lo : (lo >> off) | (hi << (64u - off));
+      w = U2{uint32_t(both), uint32_t(both >> 32)};
+    }
+    transpose64(w.a, w.b);
+    later = w.b;
+    word = (t & 32u) ? w.b : w.a;
+    if (first) word <<= t & 31u;
   }
 
+  // The action of the next step in the top bit.
   template <class St>
-  __device__ __forceinline__ uint32_t operator()(uint32_t t, const St &) {
-    const int src = int(t & 63u);
-    U2 w{uint32_t(__builtin_amdgcn_readlane(int(b0.a), src)),
-         uint32_t(__builtin_amdgcn_readlane(int(b0.b), src))};
-    if (kAligned) {
-      // Lane L is environment 64*g0 + L, so the block word is the wave's
-      // lane mask of pushes to the right: the action is one select on it.
-      return __builtin_amdgcn_inverse_ballot_w64(
-                 (static_cast<unsigned long long>(w.b) << 32) | w.a)
-                 ? 1u
-                 : 0u;
-    }
-    const U2 w1{uint32_t(__builtin_amdgcn_readlane(int(b1.a), src)),
-                uint32_t(__builtin_amdgcn_readlane(int(b1.b), src))};
-    if ((env >> 6) != g0) w = w1;
-    return bit_of_block(w, env);
+  __device__ __forceinline__ uint32_t operator()(const St &) {
+    const uint32_t w = word;
+    word <<= 1;
+    return w;
   }
 };
 
@@ -167,14 +219,17 @@ inline Traj traj_kind(const RolloutParams &p, size_t elem) {
 // below kRowsWideMinEnvs, where those leave CUs idle or with twice the work of
 // others, of 512 (300,007 x 64: 146 and 105 us; 500,009: 152 and 168).  The
 // flags' rows do not count (4,194,240 x 64: 1,189 us by waves, 1,180 by rows).
-constexpr uint64_t kRowsMinBytes = uint64_t(384) << 20;
+// In binary16, whose rows take a CU's LDS for one block, from a little later on
+// (2,000,003 x 16, 416 MB: 154 us by rows; 1,000,003 x 35, 455 MB: 156 by
+// waves, 139 by rows).
+constexpr uint64_t kRowsMinBytes = uint64_t(384) << 20, kRowsMinBytes16 = uint64_t(432) << 20;
 constexpr uint32_t kRowsWideMinEnvs = 400000;
 
 inline bool by_rows(const RolloutParams &p, size_t elem) {
   const uintptr_t starts = reinterpret_cast<uintptr_t>(p.obs) | reinterpret_cast<uintptr_t>(p.reward) |
                            uintptr_t(p.n * uint64_t(elem < 4 ? elem : 4));
   return traj_kind(p, elem) == Traj::kAll && starts % 128u != 0u &&
-         uint64_t(p.n) * p.T * (4u * elem + 5u) >= kRowsMinBytes;
+         uint64_t(p.n) * p.T * (4u * elem + 5u) >= (elem < 4 ? kRowsMinBytes16 : kRowsMinBytes);
 }
 
 // Stores of one step (obs, reward and done: the step's rows).  Each plane's
@@ -241,6 +296,21 @@ __device__ __forceinline__ void take(unsigned long long m, State16 &s, const Sta
   }
 }
 
+// On the lanes of m: dst = src.
+__device__ __forceinline__ void move_on(unsigned long long m, State &dst, const State &src) {
+  unsigned long long saved;
+  asm volatile(
+      "s_and_saveexec_b64 %[sv], %[m]\n\tv_mov_b32 %[x], %[nx]\n\tv_mov_b32 %[xd], %[nxd]\n\t"
+      "v_mov_b32 %[th], %[nth]\n\tv_mov_b32 %[thd], %[nthd]\n\ts_mov_b64 exec, %[sv]"
+      : [x] "+v"(dst.x), [xd] "+v"(dst.xd), [th] "+v"(dst.th), [thd] "+v"(dst.thd), [sv] "=&s"(saved)
+      : [m] "s"(m), [nx] "v"(src.x), [nxd] "v"(src.xd), [nth] "v"(src.th), [nthd] "v"(src.thd)
+      : "scc");
+}
+template <class S>
+__device__ __forceinline__ void move_on(unsigned long long m, S &dst, const S &src) {
+  if (__builtin_amdgcn_inverse_ballot_w64(m)) dst = src;
+}
+
 // f(integral_constant 0), ..., f(integral_constant kCount - 1)
 template <class F, int... r>
 __device__ __forceinline__ void each_of(F &f, std::integer_sequence<int, r...>) {
@@ -275,23 +345,23 @@ __device__ __forceinline__ uint32_t xcd_block() {
 // 1,700 by blocks of 256 on consecutive places, 1,850 by blocks of 1,024 as
 // launched, 1,196 by those on consecutive places (aligned rows: 1,109); in
 // binary64 3,258 -> 1,949.
-template <class T, int kBlockThreads>
+template <class T, int kEnvs>
 struct RowStage {
-  T v[4][kBlockThreads];
-  uint8_t done[kBlockThreads];
+  T v[4][kEnvs];
+  uint8_t done[kEnvs];
 };
 
 // The lane's element of the block's piece of a row: the elements from the
 // first 128-byte line on come first, those before it last.
-template <int kBlockThreads>
-__device__ __forceinline__ uint32_t turned(const void *piece, uint32_t elem_bytes) {
+template <int kEnvs>
+__device__ __forceinline__ uint32_t turned(const void *piece, uint32_t elem_bytes, uint32_t at = 0u) {
   const uint32_t head = (0u - uint32_t(reinterpret_cast<uintptr_t>(piece))) & 127u;
-  return (threadIdx.x + head / elem_bytes) & uint32_t(kBlockThreads - 1);
+  return (threadIdx.x + at + head / elem_bytes) & uint32_t(kEnvs - 1);
 }
 
-// The loop.  `policy(t, s)` returns the action of step t for the lane's
-// pre-step state s; it is called by every lane of the wave at every step
-// (policies may use cross-lane operations).  P is the precision of the
+// The loop.  `policy(s)` returns, in the top bit, the action of the next step
+// for the lane's pre-step state s; it is called by every lane of the wave at
+// every step (policies may use cross-lane operations).  P is the precision of the
 // state, the step and the obs trajectory (the state and obs pointers of p
 // point at P::T values).
 //
@@ -304,7 +374,9 @@ __device__ __forceinline__ uint32_t turned(const void *piece, uint32_t elem_byte
 // the divisions' cheaper forms against the earlier loop (length counted,
 // selects, a second termination tested for at every step): 1,048,576 x 1,000
 // in binary32 1.293 -> 1.227 ms, in binary64 2.54 -> 2.04 ms; 1,024 x 200,
-// where a step costs one wave's instruction stream, 41.8 -> 33.4 us.
+// where a step costs one wave's instruction stream, 41.8 -> 33.4 us.  With
+// the actions held per lane, a ballot per compare and more than one start state
+// ahead: 1.01 and 1.85 ms, 29.9 us (0.92 and 1.85 ms on another card).
 template <Traj kTraj, class Policy, class P = PrecF32, int kBlockThreads = kResidentBlock>
 __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy &policy) {
   using T = typename P::T;
@@ -340,6 +412,16 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   uint32_t k = k0, lr = 0u, last = 0u;
   unsigned long long used = 0u;
   S nxt = P::draw(p.krst, env, k + 1u);
+  // The start states after it that the lane holds, in order: more[d] (of
+  // episode k + 2 + d) on the lanes of held[d].
+  constexpr int kMore = kTraj == Traj::kNone && Policy::kAhead ? P::kAhead - 1 : 0;
+  S more[kMore + 1];
+  unsigned long long held[kMore + 1];
+#pragma unroll
+  for (int d = 0; d <= kMore; ++d) {
+    more[d] = nxt;
+    held[d] = 0u;
+  }
   // rows of the step's trajectory outputs
   T *row_obs = reinterpret_cast<T *>(p.obs);
   float *row_reward = p.reward;
@@ -372,20 +454,19 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     const uint32_t ed = turned<kBlockThreads>(piece_d, 1u);
     if (whole || piece0 + ed < p.n) *elem<true>(piece_d, ed) = st.done[ed];
   };
-  // One step at global index t, the r-th after the last refill; `limited`:
+  // One step, the r-th after the last refill; `limited`:
   // the state is one a step produced (every step after a launch's first), its
   // angle within the limit or NaN.
-  auto step = [&](uint32_t t, auto r, auto limited) {
-    const uint32_t a = policy(t, s);
-    S o = P::template step<decltype(limited)::value>(s, a);
-    const bool d = P::done(o);
-    const unsigned long long m = __builtin_amdgcn_ballot_w64(d);
+  auto step = [&](auto r, auto limited) {
+    S o = P::template step<decltype(limited)::value>(s, policy(s));
+    const unsigned long long m = P::template done<Policy::kUnrolled>(o);
     take(m, o, nxt, lr, r);
     used |= m;
     s = o;
     if constexpr (kTraj == Traj::kRows) {
-      store_rows(d);
+      store_rows(__builtin_amdgcn_inverse_ballot_w64(m));
     } else if constexpr (kTraj != Traj::kNone) {
+      const bool d = __builtin_amdgcn_inverse_ballot_w64(m);
       if (owner) {
         if (kTraj == Traj::kAll || off32)
           store_traj<kTraj == Traj::kAll, true>(row_obs, row_reward, row_done, p.n, i, s, d);
@@ -410,10 +491,43 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     }
     return mine;
   };
-  // ... and draw the start state of the episode after their current one,
-  // each wave for its own lanes.
+  // ... and go on to the next start state they hold.  Where a lane has none
+  // left, the wave draws: every lane short of kAhead start states its next.
+  // A draw costs as much as two steps and a third of the lanes ends an
+  // episode in a round; with three (two) states ahead the wave draws after 47
+  // (57) of 100 rounds instead of after each, most of its lanes with use
+  // (1,048,576 x 1,000 in binary64 1,904 us with one, 1,852 with two, 1,848
+  // with three at a wave per SIMD fewer).
   auto refill_wave = [&](uint32_t j) {
-    if (used != 0u && count(j)) nxt = P::draw(p.krst, env, k + 1u);
+    const unsigned long long u = used;
+    if (u == 0u) return;
+    if constexpr (kMore == 0) {
+      if (count(j)) nxt = P::draw(p.krst, env, k + 1u);
+    } else {
+      count(j);
+      move_on(u, nxt, more[0]);
+      const unsigned long long none = u & ~held[0];
+#pragma unroll
+      for (int d = 0; d < kMore; ++d) {
+        if (d + 1 < kMore) move_on(u, more[d], more[d + 1]);
+        held[d] = (held[d] & ~u) | (d + 1 < kMore ? held[d + 1] & u : 0u);
+      }
+      if (none == 0u) return;
+      uint32_t episode = k + (__builtin_amdgcn_inverse_ballot_w64(none) ? 1u : 2u);
+#pragma unroll
+      for (int d = 0; d < kMore - 1; ++d)
+        episode += __builtin_amdgcn_inverse_ballot_w64(held[d]) ? 1u : 0u;
+      const S drawn = P::draw(p.krst, env, episode);
+      move_on(none, nxt, drawn);
+      unsigned long long room = ~none;  // lanes whose states before more[d] are there
+#pragma unroll
+      for (int d = 0; d < kMore; ++d) {
+        move_on(room & ~held[d], more[d], drawn);
+        const unsigned long long there = held[d];
+        held[d] |= room;
+        room = there;
+      }
+    }
   };
   // The same refill served by the block together, for the kernel writing a
   // trajectory (bound by its stores, where fewer vector instructions mean
@@ -468,24 +582,23 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   uint32_t j = 0u;  // steps done; `first`: first step of the group
   auto singles = [&](uint32_t end) {
     const uint32_t first = j;
-    for (; j < end; ++j) step(p.t0 + j, j - first, limited_angle{});
+    for (; j < end; ++j) step(j - first, limited_angle{});
     refill(first);
   };
   policy.prepare(p.t0, true);
-  step(p.t0, 0u, any_angle{});
+  step(0u, any_angle{});
   j = 1u;
   refill(0u);
   const uint32_t lead = (0u - (p.t0 + 1u)) & (kRefill - 1u);
   if (lead != 0u) singles(p.T < 1u + lead ? p.T : 1u + lead);
   for (; j + kRefill <= p.T; j += kRefill) {
-    const uint32_t t = p.t0 + j;
-    policy.prepare(t, false);
+    policy.prepare(p.t0 + j, false);
     if constexpr (Policy::kUnrolled && kTraj != Traj::kRows) {
-      auto one = [&](auto r) { step(t + uint32_t(decltype(r)::value), r, limited_angle{}); };
+      auto one = [&](auto r) { step(r, limited_angle{}); };
       each_of(one, std::make_integer_sequence<int, int(kRefill)>{});
     } else {
 #pragma unroll 1
-      for (uint32_t r = 0; r < kRefill; ++r) step(t + r, r, limited_angle{});
+      for (uint32_t r = 0; r < kRefill; ++r) step(r, limited_angle{});
     }
     refill(j);
   }
