@@ -102,6 +102,15 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+def _stream_ptr(stream):
+    """The HIP stream of a torch stream, or of torch's current one (None): the
+    handle alone, since the Stream object that torch.cuda.current_stream()
+    builds costs 2.5 us, a third of a small cp_step call, against 0.24."""
+    if stream is not None:
+        return stream.cuda_stream
+    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+
+
 def _check(code):
     if code != CP_OK:
         raise CartPoleError(code, lib().cp_last_error().decode())
@@ -140,10 +149,9 @@ class CartPoleStates:
         self.stream = None  # None = torch's current stream at call time
 
     def handle(self):
-        st = self.stream if self.stream is not None else torch.cuda.current_stream()
         h = cp_states(_ptr(self.x), _ptr(self.x_dot), _ptr(self.theta), _ptr(self.theta_dot),
                       _ptr(self.ep_index), _ptr(self.ep_len), self.n, self.env_base,
-                      self.variant, self.seed, self.t, st.cuda_stream, _ptr(self.policy_w),
+                      self.variant, self.seed, self.t, _stream_ptr(self.stream), _ptr(self.policy_w),
                       _ptr(self.workspace),
                       0 if self.workspace is None else self.workspace.numel(),
                       self.steps_per_launch, self.precision)
@@ -234,8 +242,7 @@ def cp_policy(obs, policy_w, actions, stream=None) -> None:
     stream unless one is given."""
     n = actions.numel()
     assert obs.shape == (4, n) and obs.dtype == torch.float32 and obs.is_contiguous()
-    st = stream if stream is not None else torch.cuda.current_stream()
-    _check(lib().cp_policy(_ptr(obs), n, _ptr(policy_w), _ptr(actions), st.cuda_stream))
+    _check(lib().cp_policy(_ptr(obs), n, _ptr(policy_w), _ptr(actions), _stream_ptr(stream)))
 
 
 def cp_policy_init(seed: int):
