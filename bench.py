@@ -122,7 +122,7 @@ COUNTERS = {
         "sha256_16": "1ca420919b560501", "valu_per_wave_step": 67.5, "envs_per_wave": 64, "profile": "profiles/resident_1048576x1000_valu.md"},
     "resident_f16_1048576x1000": {
         "sources": [_CSRC + "cp_resident16.hip", _CSRC + "cp_f16_table.h", _CSRC + "cp_resident.h", _CSRC + "cp_device.h", _CSRC + "cp_precision.h", _CSRC + "cp_launch.h"],
-        "sha256_16": "218c46e7555de001", "valu_per_wave_step": 66.8, "envs_per_wave": 128, "profile": "profiles/resident_1048576x1000_valu.md"},
+        "sha256_16": "11ec41f2ba39ee82", "valu_per_wave_step": 66.8, "envs_per_wave": 128, "profile": "profiles/resident_1048576x1000_valu.md"},
     # the MLP-policy rollout, 4,194,304 x 500: SQ_INSTS_VALU per wave-step and
     # the matrix cores' busy share of SIMD cycles (SQ_VALU_MFMA_BUSY_CYCLES)
     "policy_4194304x500": {

@@ -582,7 +582,7 @@ static void f16x2_sized(const RolloutParams &p, hipStream_t stream) {
 }
 
 hipError_t launch_resident_f16x2(const RolloutParams &p, hipStream_t stream) {
-  for (uint64_t j = 0; j < p.T || j == 0u; j += kMaxStepsF16x2) {
+  for (uint64_t j = 0; j < p.T; j += kMaxStepsF16x2) {
     RolloutParams q = p;
     q.t0 = p.t0 + uint32_t(j);
     q.T = uint32_t(p.T - j < kMaxStepsF16x2 ? p.T - j : kMaxStepsF16x2);
@@ -601,7 +601,7 @@ hipError_t launch_resident_f16x2(const RolloutParams &p, hipStream_t stream) {
       }
     }
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || p.T == 0u) return e;
+    if (e != hipSuccess) return e;
   }
   return hipSuccess;
 }
