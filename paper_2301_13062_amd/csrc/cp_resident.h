@@ -574,24 +574,31 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
     if constexpr (kTraj != Traj::kNone && Policy::kBlockRefill) refill_block(j);
     else refill_wave(j);
   };
-  // The launch's first step (any state), single steps up to a multiple of
-  // kRefill, rounds of kRefill steps (unrolled), the remaining steps; a
-  // refill after each of these groups.
+  // Groups of at most kRefill steps: the launch's first step (any state) with
+  // single steps up to a multiple of kRefill, rounds of kRefill steps
+  // (unrolled), the remaining steps.  An environment that ends its episode at
+  // the first step is at most kRefill - 1 steps into the next one when the group
+  // ends, so a group needs one start state.  After a group comes a refill, after
+  // the last one only its count: launches of few steps, whose refills would all
+  // be for steps that do not come, pay for none (one step of 1,048,576
+  // environments with all outputs, 16.9 -> 14.1 us).
   using any_angle = std::integral_constant<bool, false>;
   using limited_angle = std::integral_constant<bool, true>;
-  uint32_t j = 0u;  // steps done; `first`: first step of the group
-  auto singles = [&](uint32_t end) {
-    const uint32_t first = j;
+  uint32_t j = 0u;  // steps done
+  auto close = [&](uint32_t first) {  // first: the group's first step
+    if (j < p.T) refill(first);
+    else count(first);
+  };
+  auto singles = [&](uint32_t first, uint32_t end) {
     for (; j < end; ++j) step(j - first, limited_angle{});
-    refill(first);
+    close(first);
   };
   policy.prepare(p.t0, true);
   step(0u, any_angle{});
   j = 1u;
-  refill(0u);
   const uint32_t lead = (0u - (p.t0 + 1u)) & (kRefill - 1u);
-  if (lead != 0u) singles(p.T < 1u + lead ? p.T : 1u + lead);
-  for (; j + kRefill <= p.T; j += kRefill) {
+  singles(0u, p.T < 1u + lead ? p.T : 1u + lead);
+  while (j + kRefill <= p.T) {
     policy.prepare(p.t0 + j, false);
     if constexpr (Policy::kUnrolled && kTraj != Traj::kRows) {
       auto one = [&](auto r) { step(r, limited_angle{}); };
@@ -600,11 +607,12 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
 #pragma unroll 1
       for (uint32_t r = 0; r < kRefill; ++r) step(r, limited_angle{});
     }
-    refill(j);
+    j += kRefill;
+    close(j - kRefill);
   }
   if (j < p.T) {
     policy.prepare(p.t0 + j, false);
-    singles(p.T);
+    singles(j, p.T);
   }
   // Over the rollout an environment's terminations are the growth of its
   // episode index, its episode length counts from its latest termination and

@@ -493,20 +493,20 @@ __global__ __launch_bounds__(kThreads, kThreads == 1024 && kTraj != Traj::kRows 
     };
     using any_angle = std::integral_constant<bool, true>;
     using limited_angle = std::integral_constant<bool, false>;
-    // groups of steps as in the one-per-lane loop (cp_resident.h)
-    uint32_t j = 0u;
+    // groups of steps as in the one-per-lane loop (cp_resident.h), each but the
+    // last followed by a refill
+    uint32_t j = 1u;
     prepare(p.t0, true);
     step(any_angle{});
-    j = 1u;
-    refill();
     const uint32_t lead = (0u - (p.t0 + 1u)) & (kRefill - 1u);
     for (const uint32_t end = p.T < 1u + lead ? p.T : 1u + lead; j < end; ++j) step(limited_angle{});
-    refill();
-    for (; j + kRefill <= p.T; j += kRefill) {
+    if (j < p.T) refill();
+    while (j + kRefill <= p.T) {
       prepare(p.t0 + j, false);
 #pragma unroll(kTraj == Traj::kNone ? 4 : 1)
       for (uint32_t r = 0; r < kRefill; ++r) step(limited_angle{});
-      refill();
+      j += kRefill;
+      if (j < p.T) refill();
       // A trajectory's waves go on together, neighbours on one XCD, so that the
       // parts of lines that they store meet in its L2 (3,000,000 x 50: 491 ->
       // 449 us, 4,194,304 x 50: 684 -> 608, 1,000,000 x 50: 169 -> 148).
