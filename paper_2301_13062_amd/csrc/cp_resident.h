@@ -396,10 +396,11 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   const bool off32 = uint64_t(p.n) * (sizeof(T) > 4 ? sizeof(T) : 4) <= (uint64_t(1) << 32);
   const bool valid = i < p.n, owner = valid && (threadIdx.x & 63u) < Policy::kEnvsPerWave;
   const uint32_t env = p.env_base + i;
-  // Lanes past the end run the loop on a NaN state (the wave stays converged
-  // for the cross-lane operations): it never terminates.  They store nothing.
-  const T nan = T(__builtin_nanf(""));
-  S s{nan, nan, nan, nan};
+  // Lanes past the end run the loop too (the wave stays converged for the
+  // cross-lane operations) and store nothing.  They take the first step, which
+  // evaluates angles beyond 1/4 and NaN by the library's routines (1 us for the
+  // wave), at rest, and the others on a NaN state: it never terminates.
+  S s{T(0), T(0), T(0), T(0)};
   uint32_t k0 = 0u, len0 = 0u;
   if (valid) {
     s = S{px[i], pxd[i], pth[i], pthd[i]};
@@ -596,6 +597,7 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   policy.prepare(p.t0, true);
   step(0u, any_angle{});
   j = 1u;
+  if (!valid) s.x = s.xd = s.th = s.thd = T(__builtin_nanf(""));
   const uint32_t lead = (0u - (p.t0 + 1u)) & (kRefill - 1u);
   singles(0u, p.T < 1u + lead ? p.T : 1u + lead);
   while (j + kRefill <= p.T) {

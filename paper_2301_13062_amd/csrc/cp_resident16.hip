@@ -340,9 +340,11 @@ __global__ __launch_bounds__(kThreads, kThreads == 1024 && kTraj != Traj::kRows 
   // Waves wholly past the batch skip the loop (they still take part in the
   // block's totals), where the block's waves do not wait for each other.
   if (base < p.n || kTraj != Traj::kNone) {
-    // environments past the batch: NaN states never end an episode
-    const half_t nan = half_t(__builtin_nanf(""));
-    S2 s{h2{nan, nan}, h2{nan, nan}, h2{nan, nan}, h2{nan, nan}};
+    // environments past the batch: at rest for the first step, whose angles
+    // beyond the table are evaluated out of line, then NaN states, which never
+    // end an episode (cp_resident.h)
+    const half_t rest = half_t(0.0), nan = half_t(__builtin_nanf(""));
+    S2 s{h2{rest, rest}, h2{rest, rest}, h2{rest, rest}, h2{rest, rest}};
     uint32_t k[2] = {0u, 0u};
     if (v0) {
       s.x[0] = px[i0]; s.xd[0] = pxd[i0]; s.th[0] = pth[i0]; s.thd[0] = pthd[i0];
@@ -498,6 +500,8 @@ __global__ __launch_bounds__(kThreads, kThreads == 1024 && kTraj != Traj::kRows 
     uint32_t j = 1u;
     prepare(p.t0, true);
     step(any_angle{});
+    if (!v0) s.x[0] = s.xd[0] = s.th[0] = s.thd[0] = nan;
+    if (!v1) s.x[1] = s.xd[1] = s.th[1] = s.thd[1] = nan;
     const uint32_t lead = (0u - (p.t0 + 1u)) & (kRefill - 1u);
     for (const uint32_t end = p.T < 1u + lead ? p.T : 1u + lead; j < end; ++j) step(limited_angle{});
     if (j < p.T) refill();
