@@ -150,7 +150,11 @@ __device__ __forceinline__ void transpose64(uint32_t &a, uint32_t &b) {
 // owning lane and selecting by it took five at half rate).  Waves start at
 // multiples of 64 environments after the launch's first one, so either every
 // wave is aligned to a block (kAligned: the launch starts at a multiple of 64)
-// or every wave straddles two blocks and computes both.
+// or every wave straddles two blocks and computes both.  A launch of at most
+// kFew steps, one group without a refill, selects by the outputs themselves:
+// there the transposition costs more than it saves (1,048,576 environments
+// without outputs, of one step 10.9 -> 9.7 us, of two 12.1 -> 10.4, of five 13.9
+// -> 13.3; of eight 16.5 and 16.9).
 template <bool kAligned>
 struct HashPolicy {
   static constexpr bool kUnrolled = true;      // the rounds of kRefill steps
@@ -160,31 +164,49 @@ struct HashPolicy {
   U2 key;
   uint32_t g0, off;  // the wave's first block and place in it
   uint32_t word, later;  // this lane's actions from the next step on; of steps 32 .. 63
+  uint32_t few;          // the steps of a launch of at most kFew, else 0
+  static constexpr uint32_t kFew = 8u;
 
-  __device__ __forceinline__ HashPolicy(U2 k, uint32_t env) : key(k) {
+  __device__ __forceinline__ HashPolicy(U2 k, uint32_t env, uint32_t T) : key(k), few(T <= kFew ? T : 0u) {
     const uint32_t first = uint32_t(__builtin_amdgcn_readfirstlane(int(env)));
     g0 = first >> 6;
     off = first & 63u;
   }
 
+  // The wave's output of a step: bit i the action of its i-th environment.
+  __device__ __forceinline__ U2 output(uint32_t step) const {
+    const U2 w = threefry2x32(key.a, key.b, g0, step);
+    if (kAligned) return w;
+    const U2 w1 = threefry2x32(key.a, key.b, g0 + 1u, step);
+    const unsigned long long lo = (static_cast<unsigned long long>(w.b) << 32) | w.a;
+    const unsigned long long hi = (static_cast<unsigned long long>(w1.b) << 32) | w1.a;
+    const unsigned long long both = off == 0u ? lo : (lo >> off) | (hi << (64u - off));
+    return U2{uint32_t(both), uint32_t(both >> 32)};
+  }
+
   // Called before the first step of a launch and before the steps whose
   // index is a multiple of kRefill.
   __device__ __forceinline__ void prepare(uint32_t t, bool first) {
+    if (few != 0u) {
+      if (!first) return;
+      const U2 w = output(t + (threadIdx.x & (kFew - 1u)));
+      word = 0u;
+#pragma unroll 1
+      for (int k = 0; k < int(few); ++k) {
+        const uint32_t a = uint32_t(__builtin_amdgcn_readlane(int(w.a), k));
+        const uint32_t b = uint32_t(__builtin_amdgcn_readlane(int(w.b), k));
+        if (__builtin_amdgcn_inverse_ballot_w64((static_cast<unsigned long long>(b) << 32) | a))
+          word |= 0x80000000u >> k;
+      }
+      return;
+    }
     if (!first && (t & 31u) != 0u) return;
     if (!first && (t & 63u) != 0u) {
       word = later;
       return;
     }
     // rows in descending order of their steps within each half
-    const uint32_t step = (t & ~63u) + ((threadIdx.x & 63u) ^ 31u);
-    U2 w = threefry2x32(key.a, key.b, g0, step);
-    if (!kAligned) {
-      const U2 w1 = threefry2x32(key.a, key.b, g0 + 1u, step);
-      const unsigned long long lo = (static_cast<unsigned long long>(w.b) << 32) | w.a;
-      const unsigned long long hi = (static_cast<unsigned long long>(w1.b) << 32) | w1.a;
-      const unsigned long long both = off == 0u ? lo : (lo >> off) | (hi << (64u - off));
-      w = U2{uint32_t(both), uint32_t(both >> 32)};
-    }
+    U2 w = output((t & ~63u) + ((threadIdx.x & 63u) ^ 31u));
     transpose64(w.a, w.b);
     later = w.b;
     word = (t & 32u) ? w.b : w.a;

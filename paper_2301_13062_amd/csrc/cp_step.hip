@@ -654,7 +654,7 @@ hipError_t rollout_graph(const RolloutKey &k, RolloutGraph **out) {
 template <Traj kTraj, class P, bool kAligned, int kBlockThreads = kResidentBlock>
 __global__ __launch_bounds__(kBlockThreads) void k_resident(RolloutParams p) {
   const uint32_t block = kTraj == Traj::kRows ? xcd_block() : blockIdx.x;
-  HashPolicy<kAligned> policy(p.kact, p.env_base + block * kBlockThreads + threadIdx.x);
+  HashPolicy<kAligned> policy(p.kact, p.env_base + block * kBlockThreads + threadIdx.x, p.T);
   resident_rollout<kTraj, HashPolicy<kAligned>, P, kBlockThreads>(p, policy);
 }
 
