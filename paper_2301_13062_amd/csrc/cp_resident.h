@@ -228,6 +228,15 @@ struct HashPolicy {
 // wave its own environments (kAll) or the block its piece of a row (kRows).
 enum class Traj { kNone, kAny, kAll, kRows };
 
+// The kernel without tests in the loop (kAll) leaves three waves per SIMD in
+// binary32 and two in binary64, the other one (kAny) seven and five.  Fewer waves
+// store nearer to each other (4,194,304 x 5 in binary32: 124 us, kAny 135; x 32:
+// 605 and 625) and tests cost small batches (4,096 x 64: 21 us, kAny 27), but a
+// launch of few steps lacks the waves that cover its loads: one step of
+// 1,048,576 environments 14.1 and 12.5 us, two of 4,194,304 76 and 65 (binary64,
+// one step of 4,194,304: 119 and 92, two of 1,048,576 29.6 and 28.3).
+constexpr uint32_t kAllMinSteps = 4u;
+
 inline Traj traj_kind(const RolloutParams &p, size_t elem) {
   if (!p.obs && !p.reward && !p.done) return Traj::kNone;
   const bool off32 = uint64_t(p.n) * (elem > 4 ? elem : 4) <= (uint64_t(1) << 32);
@@ -337,6 +346,15 @@ __device__ __forceinline__ void move_on(unsigned long long m, S &dst, const S &s
 template <class F, int... r>
 __device__ __forceinline__ void each_of(F &f, std::integer_sequence<int, r...>) {
   (f(std::integral_constant<int, r>{}), ...);
+}
+
+// p, the same in every lane, as a scalar.
+template <class T>
+__device__ __forceinline__ T *wave_uniform(T *p) {
+  const uintptr_t v = reinterpret_cast<uintptr_t>(p);
+  const uint32_t lo = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v))));
+  const uint32_t hi = uint32_t(__builtin_amdgcn_readfirstlane(int(uint32_t(v >> 32))));
+  return reinterpret_cast<T *>(uintptr_t(hi) << 32 | lo);
 }
 
 // The lane's environment of a launch: kEnvsPerWave consecutive ones per wave;
@@ -501,6 +519,15 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
       if (kTraj >= Traj::kAll || row_obs) row_obs += 4u * size_t(p.n);
       if (kTraj >= Traj::kAll || row_reward) row_reward += p.n;
       if (kTraj >= Traj::kAll || row_done) row_done += p.n;
+      // In binary16 the rows' addresses in scalar registers: the compiler
+      // carries those of kAll in vector ones (187, two waves per SIMD; 112 and
+      // four), which in binary32 and binary64 serves long launches (kAllMinSteps).
+      // 4,194,304 x 32 from an env_base of 1: 585 -> 457 us, x 2 87 -> 65.
+      if constexpr (kTraj == Traj::kAll && sizeof(T) == 2) {
+        row_obs = wave_uniform(row_obs);
+        row_reward = wave_uniform(row_reward);
+        row_done = wave_uniform(row_done);
+      }
     }
   };
   // After the steps from the j-th of this launch on: the lanes that ended an

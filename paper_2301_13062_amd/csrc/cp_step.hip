@@ -830,7 +830,9 @@ static void resident_as(const RolloutParams &p, hipStream_t stream) {
     }
   }
   const dim3 grid((p.n + kResidentBlock - 1) / kResidentBlock), b(kResidentBlock);
-  switch (traj_kind(p, sizeof(typename P::T))) {
+  Traj kind = traj_kind(p, sizeof(typename P::T));
+  if (kind == Traj::kAll && p.T < kAllMinSteps) kind = Traj::kAny;
+  switch (kind) {
     case Traj::kNone:
       hipLaunchKernelGGL((k_resident<Traj::kNone, P, kAligned>), grid, b, 0, stream, p);
       break;
