@@ -225,7 +225,8 @@ struct MlpPolicy {
     }
   }
 
-  __device__ __forceinline__ void prepare(uint32_t, bool) {}
+  template <Group>
+  __device__ __forceinline__ void prepare(uint32_t) {}
 
   // The hidden activations of row blocks mp .. mp + kRows - 1.
   template <bool kClamp>

@@ -141,6 +141,9 @@ __device__ __forceinline__ void transpose64(uint32_t &a, uint32_t &b) {
   b = half(b);
 }
 
+// The groups of steps of a launch (resident_rollout).
+enum class Group { kFirst, kRound, kRest };
+
 // Random actions.  The actions of a 64-environment block at one step are one
 // generator output (see action_bit).  Every 64 steps each lane computes the
 // wave's output of one of the next 64 steps, and the wave transposes them, so
@@ -165,7 +168,7 @@ struct HashPolicy {
   uint32_t g0, off;  // the wave's first block and place in it
   uint32_t word, later;  // this lane's actions from the next step on; of steps 32 .. 63
   uint32_t few;          // the steps of a launch of at most kFew, else 0
-  static constexpr uint32_t kFew = 8u;
+  static constexpr uint32_t kFew = kRefill;
 
   __device__ __forceinline__ HashPolicy(U2 k, uint32_t env, uint32_t T) : key(k), few(T <= kFew ? T : 0u) {
     const uint32_t first = uint32_t(__builtin_amdgcn_readfirstlane(int(env)));
@@ -184,11 +187,13 @@ struct HashPolicy {
     return U2{uint32_t(both), uint32_t(both >> 32)};
   }
 
-  // Called before the first step of a launch and before the steps whose
-  // index is a multiple of kRefill.
-  __device__ __forceinline__ void prepare(uint32_t t, bool first) {
-    if (few != 0u) {
-      if (!first) return;
+  // Called before a group of steps, with its first step: the launch's first
+  // (kFirst) or a multiple of kRefill, of a full round (kRound) or not (kRest).
+  // A launch of at most kFew steps has no full round.
+  template <Group kGroup>
+  __device__ __forceinline__ void prepare(uint32_t t) {
+    if (kGroup != Group::kRound && few != 0u) {
+      if (kGroup == Group::kRest) return;
       const U2 w = output(t + (threadIdx.x & (kFew - 1u)));
       word = 0u;
 #pragma unroll 1
@@ -200,8 +205,8 @@ struct HashPolicy {
       }
       return;
     }
-    if (!first && (t & 31u) != 0u) return;
-    if (!first && (t & 63u) != 0u) {
+    if (kGroup != Group::kFirst && (t & 31u) != 0u) return;
+    if (kGroup != Group::kFirst && (t & 63u) != 0u) {
       word = later;
       return;
     }
@@ -210,7 +215,7 @@ struct HashPolicy {
     transpose64(w.a, w.b);
     later = w.b;
     word = (t & 32u) ? w.b : w.a;
-    if (first) word <<= t & 31u;
+    if (kGroup == Group::kFirst) word <<= t & 31u;
   }
 
   // The action of the next step in the top bit.
@@ -629,28 +634,26 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   // (unrolled), the remaining steps.  An environment that ends its episode at
   // the first step is at most kRefill - 1 steps into the next one when the group
   // ends, so a group needs one start state.  After a group comes a refill, after
-  // the last one only its count: launches of few steps, whose refills would all
-  // be for steps that do not come, pay for none (one step of 1,048,576
-  // environments with all outputs, 16.9 -> 14.1 us).
+  // a last one of single steps only its count: launches of few steps, whose
+  // refills would all be for steps that do not come, pay for none (one step of
+  // 1,048,576 environments with all outputs, 16.9 -> 14.1 us; asked after every
+  // round too, 1,024 x 200 takes 30.4 us instead of 29.0).
   using any_angle = std::integral_constant<bool, false>;
   using limited_angle = std::integral_constant<bool, true>;
   uint32_t j = 0u;  // steps done
-  auto close = [&](uint32_t first) {  // first: the group's first step
+  auto singles = [&](uint32_t first, uint32_t end) {  // first: the group's first step
+    for (; j < end; ++j) step(j - first, limited_angle{});
     if (j < p.T) refill(first);
     else count(first);
   };
-  auto singles = [&](uint32_t first, uint32_t end) {
-    for (; j < end; ++j) step(j - first, limited_angle{});
-    close(first);
-  };
-  policy.prepare(p.t0, true);
+  policy.template prepare<Group::kFirst>(p.t0);
   step(0u, any_angle{});
   j = 1u;
   if (!valid) s.x = s.xd = s.th = s.thd = T(__builtin_nanf(""));
   const uint32_t lead = (0u - (p.t0 + 1u)) & (kRefill - 1u);
   singles(0u, p.T < 1u + lead ? p.T : 1u + lead);
-  while (j + kRefill <= p.T) {
-    policy.prepare(p.t0 + j, false);
+  for (; j + kRefill <= p.T; j += kRefill) {
+    policy.template prepare<Group::kRound>(p.t0 + j);
     if constexpr (Policy::kUnrolled && kTraj != Traj::kRows) {
       auto one = [&](auto r) { step(r, limited_angle{}); };
       each_of(one, std::make_integer_sequence<int, int(kRefill)>{});
@@ -658,11 +661,10 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
 #pragma unroll 1
       for (uint32_t r = 0; r < kRefill; ++r) step(r, limited_angle{});
     }
-    j += kRefill;
-    close(j - kRefill);
+    refill(j);
   }
   if (j < p.T) {
-    policy.prepare(p.t0 + j, false);
+    policy.template prepare<Group::kRest>(p.t0 + j);
     singles(j, p.T);
   }
   // Over the rollout an environment's terminations are the growth of its
