@@ -505,16 +505,26 @@ __global__ __launch_bounds__(kThreads, kThreads == 1024 && kTraj != Traj::kRows 
     const uint32_t lead = (0u - (p.t0 + 1u)) & (kRefill - 1u);
     for (const uint32_t end = p.T < 1u + lead ? p.T : 1u + lead; j < end; ++j) step(limited_angle{});
     if (j < p.T) refill();
+    // A trajectory's waves go on together, neighbours on one XCD, so that the
+    // parts of lines that they store meet in its L2: after every eight steps
+    // (3,000,000 x 50 491 -> 449 us, 4,194,304 x 50 684 -> 608, 1,000,000 x 50
+    // 169 -> 148), the large blocks also after the first group and every four
+    // (2,000,003 x 17 164 -> 152, 1,000,003 x 76 302 -> 288, 4,000,000 x 8 152
+    // -> 132; in the small ones it would cost 20,001 x 769 343 -> 365).
+    auto together = [&](bool round) {
+      if ((kTraj == Traj::kAny || kTraj == Traj::kAll) && (round || kThreads == 1024)) __syncthreads();
+    };
+    together(false);
     while (j + kRefill <= p.T) {
       prepare(p.t0 + j, false);
 #pragma unroll(kTraj == Traj::kNone ? 4 : 1)
-      for (uint32_t r = 0; r < kRefill; ++r) step(limited_angle{});
+      for (uint32_t r = 0; r < kRefill; ++r) {
+        step(limited_angle{});
+        if (r == kRefill / 2u - 1u) together(false);
+      }
       j += kRefill;
       if (j < p.T) refill();
-      // A trajectory's waves go on together, neighbours on one XCD, so that the
-      // parts of lines that they store meet in its L2 (3,000,000 x 50: 491 ->
-      // 449 us, 4,194,304 x 50: 684 -> 608, 1,000,000 x 50: 169 -> 148).
-      if (kTraj != Traj::kNone) __syncthreads();
+      together(true);
     }
     if (j < p.T) {
       prepare(p.t0 + j, false);
