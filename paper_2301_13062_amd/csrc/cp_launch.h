@@ -47,6 +47,7 @@ struct RolloutParams {
   uint32_t *ret_sum;         // [n]
   unsigned long long *global;
   uint32_t first;            // 1: per-env statistics start at this launch
+  uint32_t ragged;           // 1: rows off the 128-byte lines (set by launch_resident)
   int32_t precision;         // 0 binary32, 1 binary64, 2 binary16: the type of the
                              // state and obs arrays (the resident kernel only)
 };

@@ -331,8 +331,8 @@ __global__ __launch_bounds__(kResidentBlock, kTiles == 1 ? 2 : 1) void k_residen
   __shared__ MlpStage stage;
   const float free = stage_weights(p.policy_w, stage);
   MlpPolicy<kTiles> policy;
-  policy.load(stage, free, lane_env<MlpPolicy<kTiles>>() >= p.n);
-  resident_rollout<kTraj>(p, policy);
+  policy.load(stage, free, lane_env<MlpPolicy<kTiles>>(blockIdx.x) >= p.n);
+  resident_rollout<kTraj>(p, policy, blockIdx.x);
 }
 
 // The policy alone (simulation and inference as separate kernels, the
@@ -351,7 +351,7 @@ __global__ __launch_bounds__(kResidentBlock, kTiles == 1 ? 2 : 1) void k_policy_
   Policy policy;
   policy.load(stage, free, false);
   const bool owner = (threadIdx.x & 63u) < Policy::kEnvsPerWave;
-  for (uint32_t i = lane_env<Policy>(), base = blockIdx.x * kEnvs; base < n;
+  for (uint32_t i = lane_env<Policy>(blockIdx.x), base = blockIdx.x * kEnvs; base < n;
        base += gridDim.x * kEnvs, i += gridDim.x * kEnvs) {
     const uint32_t ic = i < n ? i : n - 1u;
     // plane offsets in 64 bits: 3n passes 2^32 from n > 1,431,655,765

@@ -13,6 +13,7 @@
 
 #include "cp_launch.h"
 #include "cp_precision.h"
+#include "cp_rows.h"
 
 namespace cp {
 
@@ -248,24 +249,19 @@ inline Traj traj_kind(const RolloutParams &p, size_t elem) {
   return p.obs && p.reward && p.done && off32 ? Traj::kAll : Traj::kAny;
 }
 
-// Whether a launch stores by rows (Traj::kRows): rows that start off the
-// 128-byte lines, in a trajectory that the 256 MB memory-side cache does not
-// absorb (as it does up to there: 200,003 x 64 in binary32, 269 MB: 55 us by
-// waves, 75 by rows; 300,007 x 64, 403 MB: 119 and 105).  Blocks of 1,024, and
-// below kRowsWideMinEnvs, where those leave CUs idle or with twice the work of
-// others, of 512 (300,007 x 64: 146 and 105 us; 500,009: 152 and 168).  The
-// flags' rows do not count (4,194,240 x 64: 1,189 us by waves, 1,180 by rows).
-// In binary16, whose rows take a CU's LDS for one block, from a little later on
-// (2,000,003 x 16, 416 MB: 154 us by rows; 1,000,003 x 35, 455 MB: 156 by
-// waves, 139 by rows).
-constexpr uint64_t kRowsMinBytes = uint64_t(384) << 20, kRowsMinBytes16 = uint64_t(432) << 20;
-constexpr uint32_t kRowsWideMinEnvs = 400000;
+// Threads per block of a launch that stores by rows (kRows, cp_rows.h), or 0.
+inline uint32_t rows_block(const RolloutParams &p, size_t elem) {
+  if (traj_kind(p, elem) != Traj::kAll) return 0u;
+  return rows_block(p.n, p.T, uint32_t(elem), reinterpret_cast<uintptr_t>(p.obs),
+                    reinterpret_cast<uintptr_t>(p.reward));
+}
 
-inline bool by_rows(const RolloutParams &p, size_t elem) {
-  const uintptr_t starts = reinterpret_cast<uintptr_t>(p.obs) | reinterpret_cast<uintptr_t>(p.reward) |
-                           uintptr_t(p.n * uint64_t(elem < 4 ? elem : 4));
-  return traj_kind(p, elem) == Traj::kAll && starts % 128u != 0u &&
-         uint64_t(p.n) * p.T * (4u * elem + 5u) >= (elem < 4 ? kRowsMinBytes16 : kRowsMinBytes);
+// Whether a launch has trajectory rows off the 128-byte lines
+// (RolloutParams::ragged).
+inline bool rows_ragged(const RolloutParams &p, size_t elem) {
+  return traj_kind(p, elem) != Traj::kNone &&
+         !rows_on_lines(p.n, uint32_t(elem), reinterpret_cast<uintptr_t>(p.obs),
+                        reinterpret_cast<uintptr_t>(p.reward));
 }
 
 // Stores of one step (obs, reward and done: the step's rows).  Each plane's
@@ -366,13 +362,17 @@ __device__ __forceinline__ T *wave_uniform(T *p) {
 // with fewer than 64 the lanes past them run the first ones' again (the same
 // values) and store nothing.
 template <class Policy>
-__device__ __forceinline__ uint32_t lane_env() {
+__device__ __forceinline__ uint32_t lane_env(uint32_t block) {
   constexpr uint32_t kEnvs = Policy::kEnvsPerWave;
-  return (blockIdx.x * kResidentWaves + (threadIdx.x >> 6)) * kEnvs + (threadIdx.x & (kEnvs - 1u));
+  return (block * kResidentWaves + (threadIdx.x >> 6)) * kEnvs + (threadIdx.x & (kEnvs - 1u));
 }
 
 // The block's place in the batch, blocks of one XCD (every eighth is launched
-// on the same one) next to each other.
+// on the same one) next to each other: for trajectories whose rows do not start
+// on 128-byte lines (random actions; 50,001 x 952 in binary32 328 us as
+// launched, 266 so, 150,001 x 317 353 and 291, 1,000,003 x 47 339 and 290; with
+// aligned rows 4,194,240 x 64 1,201 and 1,137, but 4,194,304 x 64 1,118 and
+// 1,130, 16,777,216 x 20 1,509 and 1,606).
 __device__ __forceinline__ uint32_t xcd_block() {
   const uint32_t x = blockIdx.x & 7u, q = gridDim.x >> 3, r = gridDim.x & 7u;
   return x * q + (x < r ? x : r) + (blockIdx.x >> 3);
@@ -422,8 +422,9 @@ __device__ __forceinline__ uint32_t turned(const void *piece, uint32_t elem_byte
 // where a step costs one wave's instruction stream, 41.8 -> 33.4 us.  With
 // the actions held per lane, a ballot per compare and more than one start state
 // ahead: 1.01 and 1.85 ms, 29.9 us (0.92 and 1.85 ms on another card).
+// block: the block's place in the batch.
 template <Traj kTraj, class Policy, class P = PrecF32, int kBlockThreads = kResidentBlock>
-__device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy &policy) {
+__device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy &policy, uint32_t block) {
   using T = typename P::T;
   using S = typename P::S;
   constexpr int kWaves = kBlockThreads / 64;
@@ -436,8 +437,8 @@ __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy 
   T *const pxd = reinterpret_cast<T *>(p.xd);
   T *const pth = reinterpret_cast<T *>(p.th);
   T *const pthd = reinterpret_cast<T *>(p.thd);
-  const uint32_t piece0 = xcd_block() * uint32_t(kBlockThreads);  // kRows: the block's first one
-  const uint32_t i = kTraj == Traj::kRows ? piece0 + threadIdx.x : lane_env<Policy>();
+  const uint32_t piece0 = block * uint32_t(kBlockThreads);  // kRows: the block's first one
+  const uint32_t i = kTraj == Traj::kRows ? piece0 + threadIdx.x : lane_env<Policy>(block);
   const bool off32 = uint64_t(p.n) * (sizeof(T) > 4 ? sizeof(T) : 4) <= (uint64_t(1) << 32);
   const bool valid = i < p.n, owner = valid && (threadIdx.x & 63u) < Policy::kEnvsPerWave;
   const uint32_t env = p.env_base + i;

@@ -49,6 +49,7 @@ namespace {
 typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 
 constexpr uint32_t kEnvsPerWave = 128u;
+static_assert(kRowsBlockEnvs16 == 16u * kEnvsPerWave, "the rows blocks' 1,024 threads");
 
 static_assert(f16tab::cosines_in_range(f16tab::make_table()),
               "a table cosine outside the range the reciprocals are keyed by");
@@ -605,7 +606,7 @@ hipError_t launch_resident_f16x2(const RolloutParams &p, hipStream_t stream) {
     if (p.obs) q.obs = reinterpret_cast<float *>(reinterpret_cast<half_t *>(p.obs) + size_t(j) * 4u * p.n);
     if (p.reward) q.reward = p.reward + size_t(j) * p.n;
     if (p.done) q.done = p.done + size_t(j) * p.n;
-    if (by_rows(q, sizeof(half_t))) {
+    if (rows_block(q, sizeof(half_t)) != 0u) {
       f16x2_as<Traj::kRows, 1024>(q, stream);
     } else {
       switch (traj_kind(q, sizeof(half_t))) {

@@ -653,9 +653,9 @@ hipError_t rollout_graph(const RolloutKey &k, RolloutGraph **out) {
 
 template <Traj kTraj, class P, bool kAligned, int kBlockThreads = kResidentBlock>
 __global__ __launch_bounds__(kBlockThreads) void k_resident(RolloutParams p) {
-  const uint32_t block = kTraj == Traj::kRows ? xcd_block() : blockIdx.x;
+  const uint32_t block = kTraj == Traj::kRows || (kTraj != Traj::kNone && p.ragged) ? xcd_block() : blockIdx.x;
   HashPolicy<kAligned> policy(p.kact, p.env_base + block * kBlockThreads + threadIdx.x, p.T);
-  resident_rollout<kTraj, HashPolicy<kAligned>, P, kBlockThreads>(p, policy);
+  resident_rollout<kTraj, HashPolicy<kAligned>, P, kBlockThreads>(p, policy, block);
 }
 
 // Totals of a per-step rollout from the episode counters: over T steps an
@@ -821,15 +821,16 @@ static void resident_rows_as(const RolloutParams &p, hipStream_t stream) {
 }
 
 template <class P, bool kAligned>
-static void resident_as(const RolloutParams &p, hipStream_t stream) {
+static void resident_as(RolloutParams p, hipStream_t stream) {
   if constexpr (!std::is_same_v<P, PrecF16>) {
-    if (by_rows(p, sizeof(typename P::T))) {
-      if (p.n < kRowsWideMinEnvs) resident_rows_as<P, kAligned, 512>(p, stream);
+    if (const uint32_t threads = rows_block(p, sizeof(typename P::T))) {
+      if (threads == 512u) resident_rows_as<P, kAligned, 512>(p, stream);
       else resident_rows_as<P, kAligned, 1024>(p, stream);
       return;
     }
   }
   const dim3 grid((p.n + kResidentBlock - 1) / kResidentBlock), b(kResidentBlock);
+  p.ragged = rows_ragged(p, sizeof(typename P::T));
   Traj kind = traj_kind(p, sizeof(typename P::T));
   if (kind == Traj::kAll && p.T < kAllMinSteps) kind = Traj::kAny;
   switch (kind) {
@@ -846,7 +847,7 @@ static void resident_as(const RolloutParams &p, hipStream_t stream) {
 }
 
 template <class P>
-static void resident_as(const RolloutParams &p, hipStream_t stream) {
+static void resident_as(RolloutParams p, hipStream_t stream) {
   if (p.env_base % 64u == 0u)
     resident_as<P, true>(p, stream);
   else

@@ -1,9 +1,10 @@
 """Trajectories whose rows do not start on 128-byte lines, stored by block in
 whole rows: the whole-rollout kernel (blocks of 512 and 1,024) and the streaming
 step, against the kernels that store by waves, bit for bit.  The rows path of
-the whole-rollout kernel is chosen by the trajectory's bytes, so the sizes sit
-just past that; the other side is the same rollout in launches too short for
-it."""
+the whole-rollout kernel is chosen by the batch and the trajectory's bytes, so
+the sizes sit just past that (or, by waves, just before; the CPU test of the
+rule checks the kernel of each); the other side is the same rollout in launches
+too short for it."""
 import pytest
 import torch
 
@@ -38,12 +39,28 @@ def same(a, b):
         assert torch.equal(getattr(tr, f), getattr(tr2, f)), f
 
 
-@pytest.mark.parametrize("prec,n,T,env_base,shift", [
-    ("f32", 300007, 64, 0, 0), ("f32", 400001, 49, 37, 0), ("f32", 524289, 40, 0, 0),
-    ("f32", 500016, 41, 64, 0), ("f32", 1048576, 20, 0, 5), ("f64", 200003, 55, 0, 0),
-    ("f64", 409601, 29, 1, 0), ("f16", 1000003, 35, 0, 0), ("f16", 700002, 50, 64, 0),
-    ("f16", 1048575, 31, 64, 0), ("f16", 655360, 50, 0, 3)])
-def test_resident_rows(gpu, prec, n, T, env_base, shift):
+# precision, environments, steps, env_base, elements that the arrays are
+# shifted by, threads per block of the rows kernel (0: by waves)
+CASES = [
+    ("f32", 300007, 64, 0, 0, 512), ("f32", 400001, 49, 37, 0, 1024),
+    ("f32", 524289, 40, 0, 0, 0), ("f32", 524287, 40, 0, 0, 1024),
+    ("f32", 500016, 41, 64, 0, 1024), ("f32", 1048576, 20, 0, 5, 1024),
+    ("f64", 200003, 55, 0, 0, 512), ("f64", 409601, 29, 1, 0, 1024),
+    # the least batches, and one environment less; a long rollout of a small one
+    ("f32", 196097, 98, 0, 0, 512), ("f32", 196096, 98, 0, 5, 0),
+    ("f32", 128001, 150, 0, 0, 512), ("f32", 127999, 150, 0, 0, 0),
+    ("f64", 97793, 112, 0, 0, 512), ("f64", 97792, 112, 0, 1, 0),
+    ("f32", 4097, 4700, 0, 0, 0), ("f64", 4097, 2700, 3, 0, 0), ("f16", 10001, 7300, 0, 0, 0),
+    # binary16: a last block of a few environments, one short of full, rows off
+    # the lines by the arrays' starts alone; by waves
+    ("f16", 1000003, 73, 0, 0, 1024), ("f16", 1036287, 71, 64, 0, 1024),
+    ("f16", 1048576, 70, 0, 3, 1024), ("f16", 1000003, 35, 0, 0, 0),
+    ("f16", 700002, 50, 64, 0, 0), ("f16", 1048575, 31, 64, 0, 0),
+    ("f16", 655360, 50, 0, 3, 0), ("f16", 1100001, 66, 0, 0, 0)]
+
+
+@pytest.mark.parametrize("prec,n,T,env_base,shift,block", CASES)
+def test_resident_rows(gpu, prec, n, T, env_base, shift, block):
     whole = rollout(cp.CP_RESIDENT, n, T, prec, env_base, 0, shift)
     same(whole, rollout(cp.CP_RESIDENT, n, T, prec, env_base, 7))
 
