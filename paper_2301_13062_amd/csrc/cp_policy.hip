@@ -370,8 +370,13 @@ __global__ __launch_bounds__(kResidentBlock, kTiles == 1 ? 2 : 1) void k_policy_
 // 10,007 environments: four tiles 228 us, two 123, one 75; of 49,152:
 // 228, 200, 170); two tiles up to 131,072 (65,536: 228, 200, one tile 216;
 // 131,072: four 369, two 364); above, four, which repeat no dynamics (262,144:
-// 683, two 715).
+// 683, two 715).  A block stages the weights and gathers its fragments before
+// its first step, so short rollouts take one tile only up to 8,192 environments
+// per step (one step of 49,152: one tile 15.9 us, two 11.7; of 16,384: 9.4 and
+// 8.4; of 4,096: 7.0 and 7.3; two steps of 24,576: 12.2 and 11.3; four of
+// 32,768: 16.0 and 15.9).
 constexpr uint32_t kOneTileMaxEnvs = 49152, kTwoTilesMaxEnvs = 131072;
+constexpr uint32_t kOneTileEnvsPerStep = 8192;
 
 template <int kTiles>
 static void actions_as(const float *obs, uint32_t n, const uint16_t *policy_w, uint8_t *actions,
@@ -411,7 +416,7 @@ static void policy_as(const RolloutParams &p, hipStream_t stream) {
 }
 
 hipError_t launch_resident_policy(const RolloutParams &p, hipStream_t stream) {
-  if (p.n <= kOneTileMaxEnvs) policy_as<1>(p, stream);
+  if (p.n <= kOneTileMaxEnvs && p.n <= uint64_t(kOneTileEnvsPerStep) * p.T) policy_as<1>(p, stream);
   else if (p.n <= kTwoTilesMaxEnvs) policy_as<2>(p, stream);
   else policy_as<4>(p, stream);
   return hipGetLastError();

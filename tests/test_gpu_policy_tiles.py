@@ -95,3 +95,25 @@ def test_policy_alone(gpu, kind):
         part = torch.empty(m, dtype=torch.uint8, device="cuda")
         cp.cp_policy(st[:, :m].contiguous(), w, part)
         assert torch.equal(part, ref[:m])
+
+
+@pytest.mark.parametrize("n", [8192, 8193, 16385, 40961])
+@pytest.mark.parametrize("traj", [False, True])
+def test_short_rollouts(gpu, n, traj):
+    """Tiles by the launch's steps: a rollout in pieces on both sides of the
+    rule (8,192 environments per step) against one launch."""
+    w, st = weights("usual"), states(n)
+    ref, rtr = rollout(w, st, n, traj)
+    for per_launch in (1, 2, 4, 5):
+        print(n, traj, per_launch, flush=True)
+        s = cp.CartPoleStates(n, variant=cp.CP_RESIDENT, policy_w=w, steps_per_launch=per_launch)
+        cp.cp_init(s, 1)
+        for dst, src in zip((s.x, s.x_dot, s.theta, s.theta_dot), st):
+            dst.copy_(src)
+        tr = cp.Trajectory(n, T, obs=traj, reward=traj, done=traj)
+        cp.cp_rollout(s, T, 0, tr)
+        torch.cuda.synchronize()
+        assert torch.equal(bits(s.state()), bits(ref.state()))
+        assert torch.equal(s.ep_index, ref.ep_index) and torch.equal(tr.ret_sum, rtr.ret_sum)
+        if traj:
+            assert torch.equal(bits(tr.obs), bits(rtr.obs)) and torch.equal(tr.done, rtr.done)
