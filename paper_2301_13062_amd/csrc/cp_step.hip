@@ -380,24 +380,27 @@ __global__ __launch_bounds__(kStreamRowBlock) void k_stream_rows(StepParams p, u
                                             n_done, ret);
 }
 
-template <Phase kPhase, bool kOff32>
+// kTotals (a last step only): see kTotalsBlocks.  Without totals the last step
+// is one environment per lane like the others: with the totals' loop and
+// barrier 16,777,216 x 3 took 4% longer.
+template <Phase kPhase, bool kOff32, bool kTotals>
 __global__ __launch_bounds__(kBlock) void k_stream_step(StepParams p, uint32_t j, uint32_t T,
                                                         unsigned long long *global) {
   uint32_t n_done, ret;
-  if (kPhase != Phase::kLast) {
+  if constexpr (!kTotals) {
     stream_one<kPhase, kOff32, 0>(p, blockIdx.x * kBlock + threadIdx.x, j, T, n_done, ret);
-    return;
+  } else {
+    __shared__ BlockTotals<kBlock> totals;
+    totals.clear();
+    __syncthreads();
+    unsigned long long all_done = 0u, all_ret = 0u;
+    for (uint32_t base = blockIdx.x * kBlock; base < p.n; base += gridDim.x * kBlock) {
+      stream_one<kPhase, kOff32, 0>(p, base + threadIdx.x, j, T, n_done, ret);
+      all_done += n_done;
+      all_ret += ret;
+    }
+    totals.publish(global, all_done, all_ret);
   }
-  __shared__ BlockTotals<kBlock> totals;
-  totals.clear();
-  __syncthreads();
-  unsigned long long all_done = 0u, all_ret = 0u;
-  for (uint32_t base = blockIdx.x * kBlock; base < p.n; base += gridDim.x * kBlock) {
-    stream_one<kPhase, kOff32, 0>(p, base + threadIdx.x, j, T, n_done, ret);
-    all_done += n_done;
-    all_ret += ret;
-  }
-  if (global) totals.publish(global, all_done, all_ret);
 }
 
 // Concatenated-state level (the paper's baseline before its "no concat"
@@ -740,11 +743,20 @@ static void stream_as(const StepParams &p, uint32_t j, uint32_t T,
       return;
     }
   }
-  if (kPhase == Phase::kLast && global && g.x > kTotalsBlocks) g.x = kTotalsBlocks;
+  if constexpr (kPhase == Phase::kLast) {
+    if (global) {
+      if (g.x > kTotalsBlocks) g.x = kTotalsBlocks;
+      if (p.n < kOff32MaxEnvs)
+        hipLaunchKernelGGL((k_stream_step<kPhase, true, true>), g, b, 0, stream, p, j, T, global);
+      else
+        hipLaunchKernelGGL((k_stream_step<kPhase, false, true>), g, b, 0, stream, p, j, T, global);
+      return;
+    }
+  }
   if (p.n < kOff32MaxEnvs)
-    hipLaunchKernelGGL((k_stream_step<kPhase, true>), g, b, 0, stream, p, j, T, global);
+    hipLaunchKernelGGL((k_stream_step<kPhase, true, false>), g, b, 0, stream, p, j, T, global);
   else
-    hipLaunchKernelGGL((k_stream_step<kPhase, false>), g, b, 0, stream, p, j, T, global);
+    hipLaunchKernelGGL((k_stream_step<kPhase, false, false>), g, b, 0, stream, p, j, T, global);
 }
 
 hipError_t launch_stream_step(const StepParams &p, uint32_t j, uint32_t T,
