@@ -666,24 +666,53 @@ __global__ __launch_bounds__(kBlockThreads) void k_resident(RolloutParams p) {
 // returns are T + ep_len(before) - ep_len(after).  Called once before the
 // steps (after == 0) and once after them (after == 1, extra = n*T); the
 // two calls' contributions add up modulo 2^64 to the exact totals.
+// A lane takes kSumsPerLane environments at a time, to have fewer blocks and so
+// atomics (65,536 environments, a rollout of one step: 18.8 us one a lane, 8.9
+// four), their loads together (one after the other 1,024 environments took 7.8
+// us instead of 6.8).
+constexpr uint32_t kSumsPerLane = 4, kSumsPerBlock = kSumsPerLane * kBlock;
+
 __global__ __launch_bounds__(kBlock) void k_episode_sums(const uint32_t *__restrict__ ep_index,
                                                          const uint32_t *__restrict__ ep_len,
                                                          uint32_t n, int after,
                                                          unsigned long long extra,
                                                          unsigned long long *global) {
-  __shared__ BlockTotals<kBlock> totals;
-  totals.clear();
-  __syncthreads();
+  __shared__ unsigned long long waves[2][kBlock / 64];
   unsigned long long sk = 0u, sl = 0u;
-  for (uint32_t i = blockIdx.x * kBlock + threadIdx.x; i < n; i += gridDim.x * kBlock) {
-    sk += ep_index[i];
-    sl += ep_len[i];
+  for (uint32_t i = blockIdx.x * kSumsPerBlock + threadIdx.x; i < n; i += gridDim.x * kSumsPerBlock) {
+    // the loads in flight together, the ones past the end of the last one's
+    uint32_t k[kSumsPerLane], l[kSumsPerLane];
+#pragma unroll
+    for (uint32_t e = 0; e < kSumsPerLane; ++e) {
+      const uint32_t at = i + e * kBlock < n ? i + e * kBlock : n - 1u;
+      k[e] = ep_index[at];
+      l[e] = ep_len[at];
+    }
+#pragma unroll
+    for (uint32_t e = 0; e < kSumsPerLane; ++e) {
+      const bool in = i + e * kBlock < n;
+      sk += in ? k[e] : 0u;
+      sl += in ? l[e] : 0u;
+    }
   }
   const unsigned long long zero = 0u;
   unsigned long long dk = after ? sk : zero - sk;
   unsigned long long dl = after ? zero - sl : sl;
   if (after && blockIdx.x == 0 && threadIdx.x == 0) dl += extra;
-  totals.publish(global, dk, dl);
+  // the waves end together, so a barrier costs less here than BlockTotals
+  dk = wave_sum_u64(dk);
+  dl = wave_sum_u64(dl);
+  if ((threadIdx.x & 63u) == 0u) {
+    waves[0][threadIdx.x >> 6] = dk;
+    waves[1][threadIdx.x >> 6] = dl;
+  }
+  __syncthreads();
+  if (threadIdx.x < 2u) {
+    unsigned long long t = 0u;
+#pragma unroll
+    for (int w = 0; w < kBlock / 64; ++w) t += waves[threadIdx.x][w];
+    if (t) atomicAdd(&global[threadIdx.x], t);
+  }
 }
 
 inline dim3 grid_for(uint32_t threads) { return dim3((threads + kBlock - 1) / kBlock); }
@@ -882,8 +911,8 @@ hipError_t launch_resident(const RolloutParams &p, hipStream_t stream) {
 hipError_t launch_episode_sums(const uint32_t *ep_index, const uint32_t *ep_len, uint32_t n,
                                bool after, unsigned long long extra, unsigned long long *global,
                                hipStream_t stream) {
-  // four environments per lane at least (fewer atomics), 1,024 blocks at most
-  const uint32_t per_block = 4u * kBlock, want = (n + per_block - 1u) / per_block;
+  // 1,024 blocks at most
+  const uint32_t want = (n + kSumsPerBlock - 1u) / kSumsPerBlock;
   const uint32_t blocks = want < 1024u ? want : 1024u;
   hipLaunchKernelGGL(k_episode_sums, dim3(blocks), dim3(kBlock), 0, stream, ep_index, ep_len, n,
                      after ? 1 : 0, extra, global);
