@@ -30,7 +30,9 @@
  *    then gives a message (per calling thread).  Arguments are validated
  *    before any HIP call: on CP_ERR_NULL/SIZE/ALIGN/RANGE/UNSUPPORTED/OVERLAP
  *    nothing is launched and *s is unchanged.  CP_ERR_HIP reports a failed
- *    launch; the handle's arrays then hold unspecified values.
+ *    launch; the handle's arrays and the call's outputs then hold unspecified
+ *    values (a rollout's per-environment statistics, which the per-step
+ *    levels complete at its last step, among them).
  *  - Outputs must not overlap the state arrays, the policy weights or each
  *    other: cp_step, cp_rollout and cp_tune_steps_per_launch compare the
  *    byte ranges of every output they are given with those of the state
