@@ -102,13 +102,18 @@ def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
+# torch's handle of a device's current stream; not a documented function, so a
+# torch without it takes the documented way.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream_ptr(stream):
     """The HIP stream of a torch stream, or of torch's current one (None): the
     handle alone, since the Stream object that torch.cuda.current_stream()
     builds costs 2.5 us, a third of a small cp_step call, against 0.24."""
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    if stream is None and _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return (stream if stream is not None else torch.cuda.current_stream()).cuda_stream
 
 
 def _check(code):
