@@ -176,7 +176,7 @@ __device__ __forceinline__ void sincos_th(float th, float &sn, float &c) {
 // multiply-add (Brisebarre, Muller and Raina, "Accelerating correctly
 // rounded floating-point division when the divisor is known in advance",
 // IEEE Trans. Computers 53(8), 2004).  Checked against correctly rounded
-// division for every binary32 significand: identical whenever |x| >= 2^-104;
+// division for every finite binary32 dividend: identical whenever |x| >= 2^-104;
 // below that (where the low product underflows) the two may differ in the
 // last place.  One operation fewer than the product corrected by its exact
 // residual, which gives the same values.
@@ -203,9 +203,9 @@ __device__ __forceinline__ float div_rn(float a, float b) {
 // a / b for the divisors of the angular acceleration at angles up to 1/4,
 // 0.621212 <= b <= 0.623995: there a line is within 3e-6 of 1/b, and one
 // Newton step from it gives the correctly rounded reciprocal for every
-// binary32 b of the range (checked exhaustively), so the quotient corrected
-// once with the exact residual is the correctly rounded quotient (Markstein).
-// Against div_rn (the same values there, checked exhaustively) a full-rate
+// binary32 b of the range (checked for each), so the quotient corrected once
+// with the exact residual is the correctly rounded quotient (Markstein; 200
+// random quotients checked for each b).  Against div_rn a full-rate
 // multiply-add takes the place of the hardware reciprocal, which issues at a
 // quarter of the rate.
 constexpr float kRecipSlope = -0x1.4a3564p+1f, kRecipOffset = 0x1.9b2d86p+1f;

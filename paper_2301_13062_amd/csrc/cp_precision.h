@@ -5,8 +5,9 @@
 // library.
 //
 // Arithmetic contract (compiled with -ffp-contract=off):
-//   binary64 -- every operation rounded once in binary64, in the operation
-//     order of the binary32 step; the three divisions by the total mass M are
+//   binary64 -- every operation rounded once in binary64 (a division but for
+//     the exception at div_small_angle64), in the operation order of the
+//     binary32 step; the three divisions by the total mass M are
 //     products with 1/M held as a sum of two numbers (the correctly rounded
 //     quotient away from underflow), the angular-acceleration division is a
 //     product with a Newton reciprocal corrected by its exact residual at
@@ -128,9 +129,12 @@ __device__ __forceinline__ double div_mass64(double x) {
 // a / b for the divisors of the angular acceleration at angles up to 1/4,
 // 0.6212 < b < 0.6240: a line within 3e-6 of 1/b and two Newton steps give
 // the reciprocal to half an ulp and 1e-22, the quotient is corrected once
-// with the exact residual: the correctly rounded quotient unless a / b lies
-// within about 2^-105 of a rounding boundary.  Eight multiply-adds instead
-// of the IEEE sequence's scaling, quarter-rate reciprocal and fix-up.
+// with the exact residual: the correctly rounded quotient wherever the
+// reciprocal is the rounded one (Markstein), and where 1/b lies within 1e-22
+// of a rounding boundary, for about one divisor in 10^6, unless a / b lies
+// within about 2^-106 of one too (no wrong quotient among random ones and the
+// closest to a boundary of random divisors).  Eight multiply-adds instead of
+// the IEEE sequence's scaling, quarter-rate reciprocal and fix-up.
 __device__ __forceinline__ double div_small_angle64(double a, double b) {
   const double y0 = __builtin_fma(b, double(kRecipSlope), double(kRecipOffset));
   const double y1 = __builtin_fma(__builtin_fma(-b, y0, 1.0), y0, y0);

@@ -4,8 +4,9 @@
 // One lane owns one environment for all T steps; its state never leaves
 // VGPRs.  Per step: the action (from the policy functor), dynamics,
 // termination; on termination the lane swaps in the start state of its next
-// episode, drawn ahead of time, and the lanes that used theirs draw the next
-// one in a batched pass every kRefill steps.
+// episode, drawn ahead of time.  After every kRefill steps at most the lanes
+// that used theirs go on to the next one they hold (up to three, without a
+// trajectory), and where a lane has none left the wave or the block draws.
 #pragma once
 
 #include <type_traits>
@@ -411,8 +412,8 @@ __device__ __forceinline__ uint32_t turned(const void *piece, uint32_t elem_byte
 // point at P::T values).
 //
 // What bounds it is vector issue (the trajectory form: its stores), so the
-// step is kept to the arithmetic, two compares, the action's lane reads and
-// select and five moves: the episode length is not counted (the step of the
+// step is kept to the arithmetic, two compares, the action's bit and shift
+// and five moves: the episode length is not counted (the step of the
 // latest termination is kept instead), the episode index is brought up to
 // date at the refills only, and rounds start at multiples of kRefill of the
 // global step, so that the generator test runs once per round.  Measured with
@@ -421,7 +422,8 @@ __device__ __forceinline__ uint32_t turned(const void *piece, uint32_t elem_byte
 // in binary32 1.293 -> 1.227 ms, in binary64 2.54 -> 2.04 ms; 1,024 x 200,
 // where a step costs one wave's instruction stream, 41.8 -> 33.4 us.  With
 // the actions held per lane, a ballot per compare and more than one start state
-// ahead: 1.01 and 1.85 ms, 29.9 us (0.92 and 1.85 ms on another card).
+// ahead: 0.92 and 1.85 ms, 29.2 us.
+//
 // block: the block's place in the batch.
 template <Traj kTraj, class Policy, class P = PrecF32, int kBlockThreads = kResidentBlock>
 __device__ __forceinline__ void resident_rollout(const RolloutParams &p, Policy &policy, uint32_t block) {
