@@ -45,6 +45,7 @@ CASES = [
     ("f32", 300007, 64, 0, 0, 512), ("f32", 400001, 49, 37, 0, 1024),
     ("f32", 524289, 40, 0, 0, 0), ("f32", 524287, 40, 0, 0, 1024),
     ("f32", 500016, 41, 64, 0, 1024), ("f32", 1048576, 20, 0, 5, 1024),
+    ("f32", 2500009, 8, 0, 0, 1024),
     ("f64", 200003, 55, 0, 0, 512), ("f64", 409601, 29, 1, 0, 1024),
     # the least batches, and one environment less; a long rollout of a small one
     ("f32", 196097, 98, 0, 0, 512), ("f32", 196096, 98, 0, 5, 0),
