@@ -105,29 +105,29 @@ COUNTERS = {
     # rollout's launches (1 first, 98 middle, 1 last)
     "stream_step_16777216": {
         "sources": [_CSRC + "cp_step.hip", _CSRC + "cp_device.h", _CSRC + "cp_launch.h"],
-        "sha256_16": "df2d30f07c8aa5e1", "fetch_kib": 157393.2, "write_kib": 388467.3, "profile": "profiles/stream_step_16777216x100_hbm.md"},
+        "sha256_16": "be751036d5d046dc", "fetch_kib": 157400.8, "write_kib": 388467.2, "profile": "profiles/stream_step_16777216x100_hbm.md"},
     # HBM traffic of one launch-bound launch (graph-replayed fused step,
     # 65,536 environments): FETCH_SIZE and WRITE_SIZE, KiB per dispatch
     "fused_step_65536": {
         "sources": [_CSRC + "cp_step.hip", _CSRC + "cp_device.h", _CSRC + "cp_launch.h"],
-        "sha256_16": "df2d30f07c8aa5e1", "fetch_kib": 814.8, "write_kib": 2702.9, "profile": "profiles/fused_step_65536env_trace_and_traffic.md"},
+        "sha256_16": "be751036d5d046dc", "fetch_kib": 815.3, "write_kib": 2702.8, "profile": "profiles/fused_step_65536env_trace_and_traffic.md"},
     # the resident rollout, 1,048,576 x 1,000: SQ_INSTS_VALU per wave-step
     "resident_1048576x1000": {
         "sources": [_CSRC + "cp_step.hip", _CSRC + "cp_resident.h", _CSRC + "cp_device.h", _CSRC + "cp_precision.h", _CSRC + "cp_launch.h"],
-        "sha256_16": "1ca420919b560501", "valu_per_wave_step": 61.0, "envs_per_wave": 64, "profile": "profiles/resident_1048576x1000_valu.md"},
+        "sha256_16": "9be10ddc52c2c950", "valu_per_wave_step": 61.0, "envs_per_wave": 64, "profile": "profiles/resident_1048576x1000_valu.md"},
     # the same rollout stepped in binary64 and in binary16 (the binary16 kernel
     # holds two environments per lane: 128 per wave)
     "resident_f64_1048576x1000": {
         "sources": [_CSRC + "cp_step.hip", _CSRC + "cp_resident.h", _CSRC + "cp_device.h", _CSRC + "cp_precision.h", _CSRC + "cp_launch.h"],
-        "sha256_16": "1ca420919b560501", "valu_per_wave_step": 67.5, "envs_per_wave": 64, "profile": "profiles/resident_1048576x1000_valu.md"},
+        "sha256_16": "9be10ddc52c2c950", "valu_per_wave_step": 67.5, "envs_per_wave": 64, "profile": "profiles/resident_1048576x1000_valu.md"},
     "resident_f16_1048576x1000": {
         "sources": [_CSRC + "cp_resident16.hip", _CSRC + "cp_f16_table.h", _CSRC + "cp_resident.h", _CSRC + "cp_device.h", _CSRC + "cp_precision.h", _CSRC + "cp_launch.h"],
-        "sha256_16": "11ec41f2ba39ee82", "valu_per_wave_step": 66.8, "envs_per_wave": 128, "profile": "profiles/resident_1048576x1000_valu.md"},
+        "sha256_16": "0e278eaa004e5532", "valu_per_wave_step": 66.6, "envs_per_wave": 128, "profile": "profiles/resident_1048576x1000_valu.md"},
     # the MLP-policy rollout, 4,194,304 x 500: SQ_INSTS_VALU per wave-step and
     # the matrix cores' busy share of SIMD cycles (SQ_VALU_MFMA_BUSY_CYCLES)
     "policy_4194304x500": {
         "sources": [_CSRC + "cp_policy.hip", _CSRC + "cp_resident.h", _CSRC + "cp_device.h", _CSRC + "cp_precision.h", _CSRC + "cp_launch.h"],
-        "sha256_16": "4f543e3e3e345de7", "valu_per_wave_step": 1547.8, "envs_per_wave": 64, "mfma_busy": 0.274, "profile": "profiles/policy_4194304x500_mfma_valu.md"},
+        "sha256_16": "10f44208efcdca26", "valu_per_wave_step": 1547.7, "envs_per_wave": 64, "mfma_busy": 0.274, "profile": "profiles/policy_4194304x500_mfma_valu.md"},
 }
 # The same counters' reading for a plain 1 GiB copy (1 GiB read, 1 GiB
 # written): bytes per KiB counted.
